@@ -156,6 +156,8 @@ template <typename R> inline size_t dots_per_rhs(const Ctx &c) {
 }
 
 dda_status device_alloc(void **p, size_t bytes);
+// a small host table to device memory, ordered on stream s, without waiting for it
+dda_status put_table(void *dst, const void *src, size_t bytes, hipStream_t s);
 
 // the opaque ABI handle is the context itself
 inline Ctx *cx(dda_ctx *p) { return reinterpret_cast<Ctx *>(p); }

@@ -137,9 +137,7 @@ dda_status material_prepare(Ctx &c, const dda_beam *beams, int n) {
     if (st != DDA_OK) return st;
     std::vector<double2> t((size_t)n * c.nmat * 3);
     for (int r = 0; r < n; ++r) material_betas(c, beams[r], t.data() + (size_t)r * c.nmat * 3);
-    DDA_HIP_CHECK(hipMemcpyAsync(c.mat_beta, t.data(), t.size() * sizeof(double2), hipMemcpyHostToDevice, c.stream));
-    DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
-    return DDA_OK;
+    return put_table(c.mat_beta, t.data(), t.size() * sizeof(double2), c.stream);
 }
 
 dda_status material_scale(Ctx &c, const dda_beam &b, const double2 *x, double2 *P, hipStream_t s) {

@@ -57,8 +57,6 @@ dda_status scratch_address(void **out) {
     *out = scratch_ptr[dev];
     return DDA_OK;
 }
-
-__global__ void k_put_scale(double2 *p, double re, double im) { *p = make_double2(re, im); }
 }  // namespace
 
 // bytes of scratch the product of one vector on this context needs: B1, B2, scale (256-aligned)
@@ -112,7 +110,8 @@ extern "C" dda_status dda_matvec_noalloc(dda_ctx *h, const dda_beam *beam, const
     double ar, ai;
     polarizability(*c, *beam, ar, ai);
     const double inv = 1.0 / ((double)c->Lx * c->Ly * c->Lz);
-    hipLaunchKernelGGL(k_put_scale, dim3(1), dim3(1), 0, c->stream, wk.scale, ar * inv, ai * inv);
+    const double2 sc = make_double2(ar * inv, ai * inv);
+    if ((st = put_table(wk.scale, &sc, sizeof sc, c->stream)) != DDA_OK) return st;
     return matvec_device_impl<double>(*c, (const double2 *)x, (double2 *)y, 1, wk.scale, nullptr, c->stream, nullptr,
                                       nullptr, &wk);
 }

@@ -952,9 +952,7 @@ template <typename R> static dda_status upload_scales(Ctx &c, const std::vector<
     std::vector<cplx<R>> sc(ar.size());
     const double inv = 1.0 / ((double)c.Lx * c.Ly * c.Lz);
     for (size_t r = 0; r < ar.size(); ++r) sc[r] = mk<cplx<R>>((R)(ar[r] * inv), (R)(ai[r] * inv));
-    DDA_HIP_CHECK(hipMemcpyAsync(w.scale, sc.data(), sc.size() * sizeof(cplx<R>), hipMemcpyHostToDevice, c.stream));
-    DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
-    return DDA_OK;
+    return put_table(w.scale, sc.data(), sc.size() * sizeof(cplx<R>), c.stream);
 }
 
 static dda_status ensure_bufs(Ctx &c, Bufs &B, int nrhs, int hcap) {
