@@ -125,18 +125,14 @@ __host__ __device__ constexpr FftPlan make_plan(int L, int maxr, int order) {
     return p;
 }
 
-// threads per line of the fused z pass: one butterfly per thread in every pass when that fits
-// in 64 (tpl1), else L / (largest radix) with several butterflies per thread in the passes of
-// smaller radix (384 = 8 4 4 3: 48 threads, not 128)
-// z-pass mode of a length.  One butterfly per thread in every pass (tpl1 threads per line, one
-// column per round) where that fits in 64 threads and a line fills a good part of a wave;
-// otherwise ("multi") L / (largest radix) threads per line, the forward plan with its largest
-// radix last, several butterflies per thread in the other passes, each component in a wave of
-// its own, and 64 / lanes columns per round (lanes = tpl rounded up to a power of two, at least
-// 16): a short line alone would leave most of a wave idle through a round's whole chain of
-// passes.  Measured per 2-vector z pass against one column per round: 48 -41 %, 64 -57 %, 96
-// -23 %, 120 -19 %, 192 -7 %, 256 -11 %; but 160 (20 of 32 lanes busy) +16 % and 72 (9 of 16)
-// +0 %, which keep one column per round.
+// Mode of the z pass of a length planned at run time (k_zmul): one butterfly per thread in every
+// pass (tpl1 threads per line, one column per round) where that fits in 64 threads and a line fills
+// a good part of a wave; otherwise ("multi") L / (largest radix) threads per line, the forward plan
+// with its largest radix last, several butterflies per thread in the other passes, each component
+// in a wave of its own, and 64 / lanes columns per round (lanes = tpl rounded up to a power of two,
+// at least 16): a short line alone would leave most of a wave idle through a round's chain of
+// passes.  The default padding of an axis admits the lengths whose line this gives at most 64
+// threads.
 __host__ __device__ constexpr int zmul_pow2_lanes(int tpl) {
     int w = 16;
     while (w < tpl) w *= 2;
@@ -152,12 +148,6 @@ __host__ __device__ constexpr int zmul_lanes(const FftPlan &p) { return zmul_mul
 __host__ __device__ constexpr int zmul_slots(const FftPlan &p) { return zmul_multi(p) ? 64 / zmul_lanes(p) : 1; }
 // threads per component in the block: a whole wave in the multi mode
 __host__ __device__ constexpr int zmul_ct(const FftPlan &p) { return zmul_multi(p) ? 64 : p.tpl1; }
-
-__host__ __device__ constexpr int pow2_at_least(int n) {
-    int w = 1;
-    while (w < n) w *= 2;
-    return w;
-}
 
 // bound on the butterflies a thread takes in a pass of radix R when a line has L / (largest
 // radix) threads and no radix exceeds maxr
@@ -331,32 +321,6 @@ template <int DIR, int RADIX, typename C> __device__ __forceinline__ void dftR(C
 // a[r] *= w^(r k) (conjugated for the inverse), w = exp(-2 pi i step / L), from the table tw.
 // With DDA_TW_DERIVED, radix 8 loads w, w^2, w^4 and forms the other four by products (fewer
 // cached loads per butterfly, ~2 ulps more rounding).
-// Twiddle source of a transform whose passes are all radix 8: the first L/8 entries of the
-// length-L table staged in LDS (lds), the full table in global memory (glob).  A radix-8 pass
-// reads w = lds[k step] (k step < L/8 there) and forms w^2, w^4 by squaring; other radices read
-// the global table.
-template <typename C> struct TwStaged {
-    const C *lds;
-    const C *glob;
-};
-
-template <int DIR, int RADIX, typename C>
-__device__ __forceinline__ void twiddle(C *a, int k, int step, TwStaged<C> tw) {
-    if constexpr (RADIX == 8) {
-        const C w1 = tw.lds[k * step], w2 = cmul(w1, w1), w4 = cmul(w2, w2);
-        const C w3 = cmul(w1, w2), w5 = cmul(w1, w4), w6 = cmul(w2, w4), w7 = cmul(w3, w4);
-        const C w[8] = {w1, w1, w2, w3, w4, w5, w6, w7};
-#pragma unroll
-        for (int r = 1; r < 8; ++r) a[r] = cmul(a[r], DIR < 0 ? w[r] : cconj(w[r]));
-    } else {
-#pragma unroll
-        for (int r = 1; r < RADIX; ++r) {
-            C w = tw.glob[r * k * step];
-            a[r] = cmul(a[r], DIR < 0 ? w : cconj(w));
-        }
-    }
-}
-
 template <int DIR, int RADIX, typename C>
 __device__ __forceinline__ void twiddle(C *a, int k, int step, const C *__restrict__ tw) {
     if constexpr (DDA_TW_DERIVED && RADIX == 8) {
@@ -386,22 +350,6 @@ __device__ __forceinline__ void bfly_load(C *a, int j, int L, int Ns, const C *_
     dftR<DIR, RADIX>(a);
 }
 
-template <int DIR, int RADIX, typename C, class LD, bool UPPER_ZERO = false>
-__device__ __forceinline__ void bfly_load(C *a, int j, int L, int Ns, TwStaged<C> tw, LD ld) {
-    const int q = L / RADIX;
-#pragma unroll
-    for (int r = 0; r < RADIX; ++r) a[r] = (UPPER_ZERO && 2 * r >= RADIX) ? czero<C>() : ld(j + r * q);
-    if (Ns > 1) twiddle<DIR, RADIX>(a, j % Ns, q / Ns, tw);
-    dftR<DIR, RADIX>(a);
-}
-
-// Twiddle and transform values already in registers (for a pass whose inputs a thread holds).
-template <int DIR, int RADIX, typename C>
-__device__ __forceinline__ void bfly_regs(C *a, int j, int L, int Ns, const C *__restrict__ tw) {
-    if (Ns > 1) twiddle<DIR, RADIX>(a, j % Ns, L / RADIX / Ns, tw);
-    dftR<DIR, RADIX>(a);
-}
-
 template <int RADIX, typename C, class ST>
 __device__ __forceinline__ void bfly_store(const C *a, int j, int Ns, ST st) {
     const int k = j % Ns;
@@ -422,34 +370,6 @@ __device__ __forceinline__ void load_rt(C *a, int R, int j, int L, int Ns, const
         case 6: bfly_load<DIR, 6, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
         case 8: if constexpr (MAXR >= 8) bfly_load<DIR, 8, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
         default: if constexpr (MAXR >= 16) bfly_load<DIR, 16, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-    }
-}
-
-template <int DIR, int MAXR, bool UPPER_ZERO = false, typename C, class LD>
-__device__ __forceinline__ void load_rt(C *a, int R, int j, int L, int Ns, TwStaged<C> tw, LD ld) {
-    switch (R) {
-        case 1: a[0] = ld(j); break;
-        case 2: bfly_load<DIR, 2, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        case 3: bfly_load<DIR, 3, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        case 4: bfly_load<DIR, 4, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        case 5: bfly_load<DIR, 5, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        case 6: bfly_load<DIR, 6, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        case 8: if constexpr (MAXR >= 8) bfly_load<DIR, 8, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-        default: if constexpr (MAXR >= 16) bfly_load<DIR, 16, C, LD, UPPER_ZERO>(a, j, L, Ns, tw, ld); break;
-    }
-}
-
-template <int DIR, int MAXR, typename C>
-__device__ __forceinline__ void regs_rt(C *a, int R, int j, int L, int Ns, const C *__restrict__ tw) {
-    switch (R) {
-        case 1: break;
-        case 2: bfly_regs<DIR, 2>(a, j, L, Ns, tw); break;
-        case 3: bfly_regs<DIR, 3>(a, j, L, Ns, tw); break;
-        case 4: bfly_regs<DIR, 4>(a, j, L, Ns, tw); break;
-        case 5: bfly_regs<DIR, 5>(a, j, L, Ns, tw); break;
-        case 6: bfly_regs<DIR, 6>(a, j, L, Ns, tw); break;
-        case 8: if constexpr (MAXR >= 8) bfly_regs<DIR, 8>(a, j, L, Ns, tw); break;
-        default: if constexpr (MAXR >= 16) bfly_regs<DIR, 16>(a, j, L, Ns, tw); break;
     }
 }
 
@@ -515,16 +435,15 @@ __device__ __forceinline__ void lds_pass(int j, int L, int tpl, int Ns, TW tw, L
 // line fits in a wave the passes sync only that wave; LC = 0 runs the runtime plan `pl`.
 // ONE: the caller runs tpl1 threads per line (one butterfly per thread in every pass) instead of
 // tpl.
-// P2: the caller gives each line a power-of-two group of lanes (threads past the line's butterfly
-// count idle), so a line whose group divides 64 lies within one wave.
-template <int DIR, int MAXR, int LC, int REV, bool ONE, bool P2, typename C, class TW>
-__device__ __forceinline__ void lds_passes_tw(C *ln, const FftPlan &pl, int p0, int p1, int j, TW tw) {
+template <int DIR, int MAXR, int LC, int REV, bool ONE = false, typename C>
+__device__ __forceinline__ void lds_passes(C *ln, const FftPlan &pl, int p0, int p1, int j,
+                                           const C *__restrict__ tw) {
     auto ld = [&](int i) { return ln[pidx(i)]; };
     auto st = [&](int i, C v) { ln[pidx(i)] = v; };
     if constexpr (LC > 0) {
         constexpr FftPlan P = make_plan(LC, MAXR, REV);
         constexpr int T = ONE ? P.tpl1 : P.tpl;
-        constexpr bool W = 64 % (P2 ? pow2_at_least(T) : T) == 0;
+        constexpr bool W = 64 % T == 0;
         static_for<1, P.npass>([&](auto pc) {
             constexpr int p = decltype(pc)::value;
             constexpr int R = P.radix[p], Ns = P.ns[p];
@@ -548,16 +467,6 @@ __device__ __forceinline__ void lds_passes_tw(C *ln, const FftPlan &pl, int p0, 
     }
 }
 
-template <int DIR, int MAXR, int LC, int REV, bool ONE = false, bool P2 = false, typename C>
-__device__ __forceinline__ void lds_passes(C *ln, const FftPlan &pl, int p0, int p1, int j,
-                                           const C *__restrict__ tw) {
-    lds_passes_tw<DIR, MAXR, LC, REV, ONE, P2>(ln, pl, p0, p1, j, tw);
-}
-template <int DIR, int MAXR, int LC, int REV, bool ONE = false, bool P2 = false, typename C>
-__device__ __forceinline__ void lds_passes(C *ln, const FftPlan &pl, int p0, int p1, int j, TwStaged<C> tw) {
-    lds_passes_tw<DIR, MAXR, LC, REV, ONE, P2>(ln, pl, p0, p1, j, tw);
-}
-
 // true when every pass of the compile-time plan of length L is radix 8 (its twiddle bases fit in
 // L/8 table entries)
 __host__ __device__ constexpr bool all_radix8(int L, int maxr) {
@@ -566,12 +475,6 @@ __host__ __device__ constexpr bool all_radix8(int L, int maxr) {
     for (int p = 0; p < P.npass; ++p)
         if (P.radix[p] != 8) return false;
     return P.npass > 0;
-}
-
-// compile-time pass count of the specialized plan (0 for the runtime plan)
-template <int LC, int MAXR> __host__ __device__ constexpr int npass_of() {
-    if constexpr (LC > 0) return make_plan(LC, MAXR, false).npass;
-    else return 0;
 }
 
 }  // namespace dda

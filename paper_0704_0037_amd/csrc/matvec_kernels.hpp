@@ -195,6 +195,7 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const cplx<R> *__res
 }
 
 // ------------------------------------------------- K3: forward z, tensor multiply, inverse z
+// for the lengths planned at run time (the specialized ones run k_zcol, zcol.hpp).
 // The (up to) four columns (kx, ky) with kx in {kxo, Lx - kxo}, ky in {kyo, Ly - kyo} share one
 // octant column (kxo, kyo) of the tensor.  A block owns one octant column: it stages the column's
 // six kz-runs in LDS once and then runs, for every right-hand side, its mirror columns through
@@ -205,18 +206,13 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const cplx<R> *__res
 // order; each thread then forms component `comp` of Ghat(k) X(k) at the frequencies k = j + r L/R0
 // that the first inverse pass (radix R0, the forward plan reversed) needs from it, straight into
 // registers.
-template <typename R, int LC>
+template <typename R>
 __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmul(cplx<R> *__restrict__ B2, const cplx<R> *__restrict__ Gh,
                                                           int nz, int Lx, int Ly, int nrhs, FftPlan pf_rt,
                                                           FftPlan pi_rt, const cplx<R> *__restrict__ twall,
                                                           const int *__restrict__ done) {
     using C = cplx<R>;
-    // multi-mode lengths run the forward plan sorted with its largest radix last and the inverse
-    // sorted largest first, so the multiply and the passes next to it keep one butterfly per thread
-    constexpr bool FLIP = LC > 0 && zmul_multi(make_plan(LC, kMaxRadixZ, false));
-    constexpr int FO = FLIP ? 2 : 0, IO = FLIP ? 3 : 1;  // plan orders (make_plan) of the two transforms
-    const FftPlan pf = plan_of<LC, kMaxRadixZ, FO>(pf_rt);
-    const FftPlan pi = plan_of<LC, kMaxRadixZ, IO>(pi_rt);
+    const FftPlan &pf = pf_rt, &pi = pi_rt;
     const int NPZ = pf.npass, RQ = pi.radix[NPZ - 1], NQ = pi.ns[NPZ - 1];
     // one butterfly per thread in every pass, or (MB) L / (largest radix) threads per line with
     // several butterflies per thread in the passes of smaller radix
@@ -248,20 +244,7 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
         const C *gcol = Gh + (size_t)oct * 6 * hz1;
         for (int e = t; e < 6 * hz1; e += blockDim.x) gsh[e] = gcol[e];
     }
-    // all-radix-8 lengths: the twiddle bases of every pass staged after the lines (no global
-    // twiddle loads inside the rounds)
-    constexpr bool TWL = LC > 0 && all_radix8(LC, kMaxRadixZ);
-    C *tws = lds + 6 * hz1 + SL * 3 * S;
-    if constexpr (TWL) {
-        for (int e = t; e < LC / 8; e += blockDim.x) tws[e] = tw[e];
-        __syncthreads();
-    }
-    const auto twp0 = [&] {
-        if constexpr (TWL) return TwStaged<C>{tws, tw};
-        else return tw;
-    }();
     C *ln = lcol + comp * S;
-    constexpr bool W = LC > 0 && 64 % zmul_lanes(make_plan(LC, kMaxRadixZ, false)) == 0;  // a line within one wave
     const int ngroups = 4 / SL;
     const bool act = j0 < qi;
     // G[comp][d] for d = x, y, z: row comp of the symmetric tensor is (xx,xy,xz), (xy,yy,yz), (xz,yz,zz)
@@ -288,10 +271,10 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
             // to the compiler from round to round, so the many per-thread LDS addresses and twiddle
             // loads are formed inside each round instead of being held in registers across rounds
             // (which spills)
-            auto twp = twp0;
+            const C *twp = tw;
             int j = j0;
             if (MB) {
-                if constexpr (!TWL) __asm__ volatile("" : "+s"(twp));
+                __asm__ volatile("" : "+s"(twp));
                 __asm__ volatile("" : "+v"(j));
             }
             const int slot = grp * SL + lslot;  // mirror 0..3 of the octant column
@@ -309,15 +292,15 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
                                         [&](int i) -> C { return (ok && i < nz) ? ld_stream(&line[i]) : czero<C>(); });
                 store_rt<kMaxRadixZ>(a, R0, jb, 1, [&](int i, C v) { ln[pidx(i)] = v; });
             }
-            lds_sync<W>();
+            lds_sync<false>();
             // LDS passes [p0, p1) of the forward (inverse) plan, one or several butterflies per thread
             auto fpasses = [&](int p0, int p1) {
-                if (MB) lds_passes<-1, kMaxRadixZ, LC, FO, false, true>(ln, pf_rt, p0, p1, j, twp);
-                else lds_passes<-1, kMaxRadixZ, LC, FO, true>(ln, pf_rt, p0, p1, j, twp);
+                if (MB) lds_passes<-1, kMaxRadixZ, 0, 0>(ln, pf_rt, p0, p1, j, twp);
+                else lds_passes<-1, kMaxRadixZ, 0, 0, true>(ln, pf_rt, p0, p1, j, twp);
             };
             auto ipasses = [&](int p0, int p1) {
-                if (MB) lds_passes<+1, kMaxRadixZ, LC, IO, false, true>(ln, pi_rt, p0, p1, j, twp);
-                else lds_passes<+1, kMaxRadixZ, LC, IO, true>(ln, pi_rt, p0, p1, j, twp);
+                if (MB) lds_passes<+1, kMaxRadixZ, 0, 0>(ln, pi_rt, p0, p1, j, twp);
+                else lds_passes<+1, kMaxRadixZ, 0, 0, true>(ln, pi_rt, p0, p1, j, twp);
             };
             // own-component path (double precision): all forward passes but the last through LDS;
             // the last one keeps this thread's outputs (its own component at kz = j + r qi) in
@@ -329,7 +312,7 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
                     fpasses(1, np - 1);
                     const int NsL = L / Ri;  // Ns of the last forward pass
                     if (act) load_rt<-1, kMaxRadixZ>(a, Ri, j, L, NsL, twp, [&](int i) { return ln[pidx(i)]; });
-                    lds_sync<W>();
+                    lds_sync<false>();
                     if (act) store_rt<kMaxRadixZ>(a, Ri, j, NsL, [&](int i, C v) { ln[pidx(i)] = v; });
                 } else if (act) {
 #pragma unroll
@@ -337,8 +320,7 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
                 }
                 __syncthreads();  // the multiply reads the other two lines and the staged tensor
             } else {
-                fpasses(1, np);  // natural order in LDS afterwards
-                if constexpr (W) __syncthreads();  // the multiply reads all three lines and the staged tensor
+                fpasses(1, np);  // natural order in LDS afterwards; the multiply reads all three lines
             }
             if (act) {
                 // signs under the mirrors: a component is odd along an axis when exactly one of its
@@ -390,23 +372,21 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
                 if (act && ok) store_rt<kMaxRadixZ>(a, Ri, j, 1, [&](int i, C v) { if (i < nz) st_stream(&line[i], v); });
             } else {
                 if (act) store_rt<kMaxRadixZ>(a, Ri, j, 1, [&](int i, C v) { ln[pidx(i)] = v; });
-                lds_sync<W>();
+                lds_sync<false>();
                 ipasses(1, np - 1);
                 for (int jb = j; jb < L / RQ; jb += TPL) {
                     load_rt<+1, kMaxRadixZ>(a, RQ, jb, L, NQ, twp, [&](int i) { return ln[pidx(i)]; });
                     if (ok) store_rt<kMaxRadixZ>(a, RQ, jb, NQ, [&](int i, C v) { if (i < nz) st_stream(&line[i], v); });
                 }
             }
-            lds_sync<W>();  // the slot's lines are rewritten by the next round
+            lds_sync<false>();  // the slot's lines are rewritten by the next round
         }
     }
 }
 
-// LDS elements of the z-pass block: the tensor column, zmul_slots slots of three lines and,
-// for all-radix-8 lengths, the staged twiddle bases
+// LDS elements of the z-pass block: the tensor column and zmul_slots slots of three lines
 __host__ __device__ constexpr size_t zmul_lds_elems(int Lz) {
-    return (size_t)6 * (Lz / 2 + 1) + (size_t)zmul_slots(make_plan(Lz, kMaxRadixZ, false)) * 3 * lds_line_stride(Lz) +
-           (all_radix8(Lz, kMaxRadixZ) ? (size_t)Lz / 8 : 0);
+    return (size_t)6 * (Lz / 2 + 1) + (size_t)zmul_slots(make_plan(Lz, kMaxRadixZ, false)) * 3 * lds_line_stride(Lz);
 }
 
 // ---------------------------------------------------------------- K4: inverse y pass

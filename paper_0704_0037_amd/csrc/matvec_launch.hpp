@@ -3,12 +3,15 @@
 // Included by one translation unit per precision.
 #pragma once
 
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <set>
 #include <tuple>
 
 #include "ctx.hpp"
 #include "matvec_kernels.hpp"
+#include "zcol.hpp"
 
 
 namespace dda {
@@ -53,9 +56,53 @@ template <class K> inline void allow_lds(K kernel, size_t bytes) {
     }
 #define DDA_CASE_k_fwd_x(L) case L: allow_lds(&k_fwd_x<R, L, RX>, DDA_BYTES); hipLaunchKernelGGL((k_fwd_x<R, L, RX>), DDA_ARGS); break;
 #define DDA_CASE_k_fwd_y(L) case L: allow_lds(&k_fwd_y<R, L>, DDA_BYTES); hipLaunchKernelGGL((k_fwd_y<R, L>), DDA_ARGS); break;
-#define DDA_CASE_k_zmul(L) case L: allow_lds(&k_zmul<R, L>, DDA_BYTES); hipLaunchKernelGGL((k_zmul<R, L>), DDA_ARGS); break;
+#define DDA_CASE_zcol(L) case L: zcol_launch<R, L>(c, w.B2, gh, nrhs, tw, s, done); break;
 #define DDA_CASE_k_inv_y(L) case L: allow_lds(&k_inv_y<R, L>, DDA_BYTES); hipLaunchKernelGGL((k_inv_y<R, L>), DDA_ARGS); break;
 #define DDA_CASE_k_inv_x(L) case L: allow_lds(&k_inv_x<R, L, RX>, DDA_BYTES); hipLaunchKernelGGL((k_inv_x<R, L, RX>), DDA_ARGS); break;
+
+// Block shape of the column kernel: up to four waves over opb octant columns, which take
+// ceil(4 nrhs opb / (W CPW)) rounds.  The smallest opb whose estimate is not beaten by 10 %: turns of
+// the grid over the resident blocks, times rounds (a tenth for staging the tensor), times a factor
+// for the waves that share a compute unit.  A wave of 3, 5 or 7 columns needs several octant
+// columns to fill its rounds (L = 160, one vector: opb 1, 3: 127, 78 us; L = 96: opb 1, 5: 36,
+// 22 us), and small grids run faster with one block per compute unit.
+struct ZShape {
+    int W, opb;
+};
+template <typename R, int LC> inline ZShape zcol_shape(int noct, int nrhs) {
+    using Z = ZCol<LC>;
+    constexpr int kCUs = 256, kWaves = 4 * zcol_waves_per_simd<R>(LC);
+    ZShape best{1, 1};
+    double cost = 1e300;
+    for (int opb = 1; opb <= 8; ++opb) {
+        const int64_t items = (int64_t)4 * nrhs * opb;
+        const int W = items > 2 * Z::CPW ? 4 : items > Z::CPW ? 2 : 1;
+        const size_t lds = zcol_lds<R, LC>(opb, W);
+        if (opb > 1 && lds > 80 * 1024) break;
+        const int per_cu = std::min<int>(160 * 1024 / (int)lds, kWaves / W);
+        const int64_t rounds = (items + W * Z::CPW - 1) / (W * Z::CPW), blocks = (noct + opb - 1) / opb;
+        const int resident = W * (int)std::min<int64_t>(per_cu, (blocks + kCUs - 1) / kCUs);
+        const double turns = (double)blocks / (kCUs * per_cu);
+        const double t = (turns < 4 ? std::ceil(turns) : turns) * (rounds + 0.1) * (8 + resident);
+        if (t < 0.9 * cost) {
+            cost = t;
+            best = {W, opb};
+        }
+    }
+    return best;
+}
+
+template <typename R, int LC>
+inline void zcol_launch(const Ctx &c, cplx<R> *B2, const cplx<R> *gh, int nrhs, const cplx<R> *tw, hipStream_t s,
+                        const int *done) {
+    const int noct = (c.Lx / 2 + 1) * (c.Ly / 2 + 1);
+    const ZShape z = zcol_shape<R, LC>(noct, nrhs);
+    const size_t lds = zcol_lds<R, LC>(z.opb, z.W);
+    const int blocks = (noct + z.opb - 1) / z.opb;
+    allow_lds(&k_zcol<R, LC>, lds);
+    hipLaunchKernelGGL((k_zcol<R, LC>), dim3((blocks + 7) / 8 * 8), dim3(64 * z.W), lds, s, B2, gh, c.nz, c.Lx, c.Ly,
+                       nrhs, z.opb, tw + c.pzf.tw_off, done);
+}
 
 // Transforms in precision R on the work buffers of precision R (the context's, or the
 // intermediates B1 / B2 of `wk` when given); x, y, scale and dots in RX.
@@ -92,12 +139,14 @@ dda_status matvec_device_impl(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, 
 #undef DDA_ARGS
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[2], s));
     const int zblocks = (c.Lx / 2 + 1) * (c.Ly / 2 + 1);  // one block per octant column
-#define DDA_ARGS dim3((zblocks + 7) / 8 * 8), dim3(3 * zmul_ct(c.pzf)), lz_bytes, s, w.B2, gh, c.nz, \
-                 c.Lx, c.Ly, nrhs, c.pzf, c.pzi, tw, done
-#define DDA_BYTES lz_bytes
-    DDA_DISPATCH(c.Lz, k_zmul, DDA_BYTES, DDA_ARGS)
-#undef DDA_BYTES
-#undef DDA_ARGS
+    switch (c.Lz) {
+        DDA_SPECIALIZED_LENGTHS(DDA_CASE_zcol)
+        default:
+            allow_lds(&k_zmul<R>, lz_bytes);
+            hipLaunchKernelGGL(k_zmul<R>, dim3((zblocks + 7) / 8 * 8), dim3(3 * zmul_ct(c.pzf)), lz_bytes, s, w.B2, gh,
+                               c.nz, c.Lx, c.Ly, nrhs, c.pzf, c.pzi, tw, done);
+            break;
+    }
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[3], s));
 #define DDA_ARGS dim3(ncomp * c.Lx * ztiles), dim3(nly * c.pyi.tpl), ly_bytes, s, w.B2, w.B1, c.ny, c.nz, c.Lx, ncomp, \
                  c.pyi, tw, tl.lnl_y, done

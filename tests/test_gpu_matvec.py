@@ -332,3 +332,22 @@ def test_many_sphere_sizes_set_up():
         with dda.Context(inputs.sphere_mask(n), 1.2, 0.3) as ctx:
             L = ctx.padded_grid()
             assert L[0] >= 2 * n - 1 and L[0] == L[1] == L[2]
+
+
+@pytest.mark.parametrize("L", [32, 60, 72, 96, 160, 192, 320])
+def test_columns_do_not_depend_on_the_batch(L):
+    """A wave of the z pass takes 16, 5, 7, 5, 3, 2 and 1 columns at these lengths, and the block's
+    shape follows the batch size: whole and partly filled rounds, blocks of one and several octant
+    columns, more octant columns than blocks can share evenly.  The arithmetic of a column is the
+    same in all of them, so a batch equals its single products bit for bit."""
+    dda = _dda()
+    mask = _random_mask((9, 7, 6), 700 + L, 0.6)  # [nz][ny][nx]
+    beams = [inputs.X_POL, inputs.Y_POL] * 5
+    with dda.Context(mask, 1.4 + 0.02j, 0.5, pad=(20, 18, L)) as ctx:
+        assert ctx.padded_grid() == (20, 18, L)
+        x = torch.from_numpy(inputs.random_vector(ctx.n, seed=L, n_rhs=9)).cuda()
+        one = torch.stack([ctx.matvec(beams[r], x[r].contiguous()) for r in range(9)])
+        for n in (2, 3, 5, 9):
+            assert torch.equal(ctx.matvec_batch(beams[:n], x[:n].contiguous()), one[:n]), n
+        ref = _oracle_y(mask, 1.4 + 0.02j, 0.5, beams[0], x[0].cpu().numpy())
+        assert _rel_err(one[0].cpu().numpy(), ref) < 1e-12
