@@ -2,12 +2,13 @@
 // sections, far-field scattering amplitudes, and the Mueller matrix in a scattering plane
 // (the quantities the paper compares with Mie theory, Sec. 3.1).
 //
-// Far field: F(n) = -i k^3 (I - n n) sum_j P_j exp(-i k n.r_j).  A block takes up to 256
-// directions (one per thread) and a range of grid lines (y, z); every thread walks the dipoles
-// of each line (read wave-uniformly through the scalar cache), advancing its phase factor along
-// x by one multiplication per cell (a direct sincos restarts the recurrence after a gap in the
-// line and at the start of every line, so at most nx - 1 products accumulate rounding).
+// Far field: F(n) = -i k^3 (I - n n) sum_j P_j exp(-i k n.r_j).  Where the directions share few
+// values of their component along a lattice axis, the sum is taken in two stages: along that axis
+// once per value (k_ff_collapse), then over the plane that is left for every direction (k_ff_plane).
+// Otherwise one stage (k_farfield) walks all dipoles for every direction.
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -74,18 +75,23 @@ __global__ void __launch_bounds__(kRoThreads) k_xsec(const double2 *__restrict__
     }
 }
 
-// F partial sums (without the -i k^3 (I - nn) beta factor) for the directions of this block
-// (one per lane) over the lines [l0, l1) of chunk blockIdx.y; writes part[(d * nchunk + chunk) * 3 + c].
+// F partial sums (without the -i k^3 (I - nn) beta factor) of vector blockIdx.z for the directions of
+// this block (one per lane; up to 256, a range of lines (y, z) each) over the lines [l0, l1) of chunk
+// blockIdx.y; writes part[(z * nchunk + chunk) * 3 ndir + 3 d + c].  Every thread advances its phase
+// factor along x by one multiplication per cell (a direct sincos restarts the recurrence after a
+// gap in the line and at the start of every line, so at most nx - 1 products accumulate rounding).
 // Every lane of a wave walks the same dipoles, so their polarizations and cell indices are
 // wave-uniform: they come through the scalar data cache into scalar registers, which the fp64
 // multiply-adds read directly (no LDS staging, no block barriers).
-__global__ void __launch_bounds__(kRoThreads) k_farfield(const double2 *__restrict__ x, const int *__restrict__ lin,
+__global__ void __launch_bounds__(kRoThreads) k_farfield(const double2 *__restrict__ xa,
+                                                         const double2 *__restrict__ xb, const int *__restrict__ lin,
                                                          const int *__restrict__ line_start, int N, int nx, int ny,
                                                          int nz, int lines_per_chunk, const double *__restrict__ dirs,
                                                          int ndir, double k, double2 *__restrict__ part) {
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = d < ndir;
     const int chunk = blockIdx.y, nchunk = gridDim.y;
+    const double2 *__restrict__ x = blockIdx.z ? xb : xa;
     double nxd = 0, nyd = 0, nzd = 0;
     if (active) {
         nxd = dirs[3 * d];
@@ -140,20 +146,142 @@ __global__ void __launch_bounds__(kRoThreads) k_farfield(const double2 *__restri
         for (; q < e; ++q) step(lin[q] - base, x[q], x1[q], x2[q]);
     }
     if (active)
-        for (int c = 0; c < 3; ++c) part[((size_t)d * nchunk + chunk) * 3 + c] = acc[c];
+        for (int c = 0; c < 3; ++c) part[((size_t)blockIdx.z * nchunk + chunk) * 3 * ndir + 3 * d + c] = acc[c];
 }
 
-__global__ void k_ff_sum(const double2 *part, int ndir, int nchunk, double2 *out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;  // (d, c)
-    if (e >= ndir * 3) return;
-    const int d = e / 3, c = e % 3;
+// sums over the chunks of part [nvec][nchunk][e3] (a block: 64 entries, 8 strided partial sums each,
+// added in a fixed order)
+__global__ void __launch_bounds__(512) k_ff_sum(const double2 *__restrict__ part, int e3, int nchunk,
+                                                double2 *__restrict__ out) {
+    __shared__ double2 sh[8][64];
+    const int lx = threadIdx.x & 63, ly = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lx;
+    const double2 *p = part + (size_t)blockIdx.y * nchunk * e3;
     double2 s = make_double2(0, 0);
-    for (int q = 0; q < nchunk; ++q) {
-        const double2 v = part[((size_t)d * nchunk + q) * 3 + c];
-        s.x += v.x;
-        s.y += v.y;
+    if (e < e3)
+        for (int q = ly; q < nchunk; q += 8) {
+            const double2 v = p[(size_t)q * e3 + e];
+            s.x += v.x;
+            s.y += v.y;
+        }
+    sh[ly][lx] = s;
+    __syncthreads();
+    if (ly == 0 && e < e3) {
+        for (int k = 1; k < 8; ++k) {
+            s.x += sh[k][lx].x;
+            s.y += sh[k][lx].y;
+        }
+        out[(size_t)blockIdx.y * e3 + e] = s;
     }
-    out[e] = s;
+}
+
+// Stage 1 of the grouped sum: Q[vec][group][c][v][u] = sum over the cells a of the column (u, v) along
+// the axis of x exp(-i k w_g p_a), w_g the groups' direction component.  A block takes 64 columns
+// (neighbours along u) and four groups; its four waves split the column and are added in LDS.  Bound
+// by reading the vector once per four groups (128^3 sphere, one group, two vectors: 106 MB and
+// the cell map in 30 us).
+constexpr int kFfGroups = 4;
+__global__ void __launch_bounds__(256) k_ff_collapse(const double2 *__restrict__ xa, const double2 *__restrict__ xb,
+                                                     const int *__restrict__ gmap, int N, int nu, int nv, int na,
+                                                     size_t su, size_t sv, size_t sa, const double *__restrict__ w,
+                                                     int ngroup, double k, double2 *__restrict__ Q) {
+    __shared__ double2 sh[3][64];
+    const double2 *__restrict__ x = blockIdx.z ? xb : xa;
+    const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6;
+    const int utiles = (nu + 63) / 64;
+    const int u = (blockIdx.x % utiles) * 64 + lane, v = blockIdx.x / utiles;
+    const int g0 = blockIdx.y * kFfGroups;
+    const int per = (na + 3) / 4, a0 = min(na, seg * per), a1 = min(na, a0 + per);
+    const size_t cell = (size_t)min(u, nu - 1) * su + (size_t)v * sv;
+    double2 acc[kFfGroups][3], ph[kFfGroups], st[kFfGroups];
+#pragma unroll
+    for (int g = 0; g < kFfGroups; ++g) {
+        const double wk = -k * w[min(g0 + g, ngroup - 1)];
+        sincos(wk, &st[g].y, &st[g].x);
+        sincos(wk * (a0 + 0.5 - 0.5 * na), &ph[g].y, &ph[g].x);
+        for (int c = 0; c < 3; ++c) acc[g][c] = make_double2(0, 0);
+    }
+    for (int a = a0; a < a1; a += 4) {  // four cells' loads in flight
+        double2 q[4][3];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int id = a + t < a1 && u < nu ? gmap[cell + (size_t)(a + t) * sa] : -1;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) q[t][c] = id >= 0 ? x[(size_t)c * N + id] : make_double2(0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int g = 0; g < kFfGroups; ++g) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    acc[g][c].x += q[t][c].x * ph[g].x - q[t][c].y * ph[g].y;
+                    acc[g][c].y += q[t][c].x * ph[g].y + q[t][c].y * ph[g].x;
+                }
+                ph[g] = make_double2(ph[g].x * st[g].x - ph[g].y * st[g].y, ph[g].x * st[g].y + ph[g].y * st[g].x);
+            }
+    }
+    const size_t plane = (size_t)nu * nv;
+#pragma unroll
+    for (int g = 0; g < kFfGroups; ++g)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (seg > 0) sh[seg - 1][lane] = acc[g][c];
+            __syncthreads();
+            if (seg == 0 && u < nu && g0 + g < ngroup) {
+                double2 s = acc[g][c];
+                for (int q = 0; q < 3; ++q) {
+                    s.x += sh[q][lane].x;
+                    s.y += sh[q][lane].y;
+                }
+                Q[(((size_t)blockIdx.z * ngroup + g0 + g) * 3 + c) * plane + (size_t)v * nu + u] = s;
+            }
+            __syncthreads();
+        }
+}
+
+// Stage 2: a wave takes up to 64 directions of one group (tile = {group, first, count}) and the rows [v0, v1) of chunk blockIdx.y of the plane; the plane's values are
+// wave-uniform and come through the scalar cache, as in k_farfield.  au, av: the axes of u and v.
+__global__ void __launch_bounds__(64) k_ff_plane(const double2 *__restrict__ Q, int nu, int nv, int ngroup,
+                                                 int rows_per_chunk, const int *__restrict__ tiles,
+                                                 const double *__restrict__ dirs, int au, int av, int ndir, double k,
+                                                 double2 *__restrict__ part) {
+    const int grp = tiles[3 * blockIdx.x], first = tiles[3 * blockIdx.x + 1], count = tiles[3 * blockIdx.x + 2];
+    const bool active = (int)threadIdx.x < count;
+    const int d = first + (active ? threadIdx.x : 0);
+    const double wu = -k * dirs[3 * d + au], wv = -k * dirs[3 * d + av];
+    double2 st;
+    sincos(wu, &st.y, &st.x);
+    const int v0 = blockIdx.y * rows_per_chunk, v1 = min(nv, v0 + rows_per_chunk);
+    const size_t plane = (size_t)nu * nv;
+    const double2 *q0 = Q + ((size_t)blockIdx.z * ngroup + grp) * 3 * plane;
+    double2 acc[3] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
+    for (int v = v0; v < v1; ++v) {
+        double2 ph;
+        sincos(wu * (0.5 - 0.5 * nu) + wv * (v + 0.5 - 0.5 * nv), &ph.y, &ph.x);
+        const double2 *r0 = q0 + (size_t)v * nu, *r1 = r0 + plane, *r2 = r1 + plane;
+        auto step = [&](double2 a, double2 b, double2 c) {
+            const double2 q[3] = {a, b, c};
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                acc[e].x += q[e].x * ph.x - q[e].y * ph.y;
+                acc[e].y += q[e].x * ph.y + q[e].y * ph.x;
+            }
+            ph = make_double2(ph.x * st.x - ph.y * st.y, ph.x * st.y + ph.y * st.x);
+        };
+        int u = 0;
+        for (; u + 4 <= nu; u += 4) {
+            double2 a[4], b[4], c[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = r0[u + t], b[t] = r1[u + t], c[t] = r2[u + t];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) step(a[t], b[t], c[t]);
+        }
+        for (; u < nu; ++u) step(r0[u], r1[u], r2[u]);
+    }
+    if (active)
+        for (int e = 0; e < 3; ++e)
+            part[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * 3 * ndir + 3 * d + e] = acc[e];
 }
 
 static dda_status ensure_red(Ctx &c, size_t elems) {
@@ -185,38 +313,136 @@ static dda_status ensure_lines(Ctx &c) {
     return DDA_OK;
 }
 
-// sum_j x_j exp(-i k n.r_j) for each direction (host [ndir][3] complex), before beta and the projector
-static dda_status farfield_sums(Ctx &c, const double2 *x, int ndir, const double *dirs, std::vector<double2> &out) {
+// The runs of neighbouring directions that share their component along one axis (a scattering plane
+// that contains two axes; a sphere of directions given ring by ring).  A component below half an
+// ulp of 1 (cos(pi / 2) in a scattering plane) counts as zero: its phase differs by less than the
+// rounding of k n.r.
+struct FfRuns {
+    int axis = -1;
+    std::vector<double> value;
+    std::vector<int> start;  // first direction of each run, then ndir
+    double tiles = 0;        // waves of directions
+};
+static FfRuns ff_runs(int axis, int ndir, const double *dirs, double most) {
+    FfRuns f;
+    for (int d = 0; d < ndir; ++d) {
+        const double t = dirs[3 * d + axis], w = std::fabs(t) < 2.3e-16 ? 0.0 : t;
+        if (d == 0 || w != f.value.back()) {
+            if (f.value.size() >= most) return FfRuns{};
+            f.value.push_back(w);
+            f.start.push_back(d);
+        }
+    }
+    f.start.push_back(ndir);
+    f.axis = axis;
+    for (size_t g = 0; g < f.value.size(); ++g) f.tiles += (f.start[g + 1] - f.start[g] + 63) / 64;
+    return f;
+}
+
+// sum_j x_j exp(-i k n.r_j) for each direction (host [ndir][3] complex) and each of the nvec (1 or 2)
+// vectors, before beta and the projector: out [nvec][ndir][3]
+static dda_status farfield_sums(Ctx &c, const double2 *xa, const double2 *xb, int ndir, const double *dirs,
+                                std::vector<double2> &out) {
     dda_status st;
-    if ((st = ensure_lines(c)) != DDA_OK) return st;
-    const int nlines = c.ny * c.nz;
-    // directions in whole waves, at most four waves a block, blocks as even as the count allows
-    const int waves = (ndir + 63) / 64;
-    const int dtiles = (waves + kRoThreads / 64 - 1) / (kRoThreads / 64);
-    const int bthreads = 64 * ((waves + dtiles - 1) / dtiles);
-    // enough chunks to fill the GPU several times over, at least a few lines each
-    int nchunk = std::max(1, std::min(nlines, 2048 / std::max(1, dtiles)));
-    const int lpc = (nlines + nchunk - 1) / nchunk;
-    nchunk = (nlines + lpc - 1) / lpc;
-    const size_t npart = (size_t)ndir * nchunk * 3;
-    if ((st = ensure_red(c, npart + (size_t)ndir * 3 + (size_t)ndir * 3 / 2 + 4)) != DDA_OK) return st;
-    double2 *part = c.red;
-    double2 *sums = c.red + npart;
-    double *ddirs = (double *)(sums + (size_t)ndir * 3);
-    DDA_HIP_CHECK(hipMemcpyAsync(ddirs, dirs, (size_t)ndir * 3 * sizeof(double), hipMemcpyHostToDevice, c.stream));
-    hipLaunchKernelGGL(k_farfield, dim3(dtiles, nchunk), dim3(bthreads), 0, c.stream, x, c.lin, c.line_start,
-                       (int)c.N, c.nx, c.ny, c.nz, lpc, ddirs, ndir, c.kd, part);
-    hipLaunchKernelGGL(k_ff_sum, dim3((ndir * 3 + 255) / 256), dim3(256), 0, c.stream, part, ndir, nchunk, sums);
+    const int nvec = xb ? 2 : 1, e3 = 3 * ndir;
+    const int n[3] = {c.nx, c.ny, c.nz};
+    // Work of the two ways, in lanes x cells: waves of directions over all dipoles; or, in runs along
+    // an axis, runs (in whole blocks of them) over all dipoles and waves of directions over the
+    // plane.  The second is taken where it does at most half the work (both inner loops run at about
+    // the same rate): 361 directions of the plane y = 0 on the 128^3 sphere, two vectors, 1515 ->
+    // 110 us, the asymmetry parameter of the 64^3 ellipsoid (21 rings of 42) 288 ->
+    // 78 us;
+    // directions in general position are a run each.
+    FfRuns best;
+    double cost = 0.5 * 64.0 * ((ndir + 63) / 64) * c.N;
+    for (int a = 2; a >= 0; --a) {
+        const double plane = (double)n[0] * n[1] * n[2] / n[a];
+        FfRuns f = ff_runs(a, ndir, dirs, cost / c.N);
+        if (f.axis < 0) continue;
+        const double t = (double)((f.value.size() + kFfGroups - 1) / kFfGroups * kFfGroups) * c.N + 64.0 * f.tiles * plane;
+        if (t < cost) {
+            cost = t;
+            best = std::move(f);
+        }
+    }
+    out.resize((size_t)nvec * e3);
+    if (best.axis < 0) {
+        if ((st = ensure_lines(c)) != DDA_OK) return st;
+        const int nlines = c.ny * c.nz;
+        // directions in whole waves, at most four waves a block, blocks as even as the count allows
+        const int waves = (ndir + 63) / 64;
+        const int dtiles = (waves + kRoThreads / 64 - 1) / (kRoThreads / 64);
+        const int bthreads = 64 * ((waves + dtiles - 1) / dtiles);
+        // enough chunks to fill the GPU several times over, at least a few lines each
+        int nchunk = std::max(1, std::min(nlines, 2048 / std::max(1, dtiles)));
+        const int lpc = (nlines + nchunk - 1) / nchunk;
+        nchunk = (nlines + lpc - 1) / lpc;
+        const size_t npart = (size_t)nvec * nchunk * e3;
+        if ((st = ensure_red(c, npart + (size_t)nvec * e3 + (size_t)e3 / 2 + 4)) != DDA_OK) return st;
+        double2 *part = c.red, *sums = part + npart;
+        double *ddirs = (double *)(sums + (size_t)nvec * e3);
+        DDA_HIP_CHECK(hipMemcpyAsync(ddirs, dirs, (size_t)e3 * sizeof(double), hipMemcpyHostToDevice, c.stream));
+        hipLaunchKernelGGL(k_farfield, dim3(dtiles, nchunk, nvec), dim3(bthreads), 0, c.stream, xa, xb, c.lin,
+                           c.line_start, (int)c.N, c.nx, c.ny, c.nz, lpc, ddirs, ndir, c.kd, part);
+        hipLaunchKernelGGL(k_ff_sum, dim3((e3 + 63) / 64, nvec), dim3(512), 0, c.stream, part, e3, nchunk,
+                           sums);
+        DDA_HIP_CHECK(hipGetLastError());
+        DDA_HIP_CHECK(hipMemcpyAsync(out.data(), sums, out.size() * sizeof(double2), hipMemcpyDeviceToHost, c.stream));
+        DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
+        return DDA_OK;
+    }
+    // axes of the plane: u the faster one
+    const int a = best.axis, au = a == 0 ? 1 : 0, av = a == 2 ? 1 : 2;
+    const size_t stride[3] = {1, (size_t)c.nx, (size_t)c.nx * c.ny};
+    const int nu = n[au], nv = n[av];
+    const size_t plane = (size_t)nu * nv;
+    // runs in batches whose planes take at most 64 MiB (one run at least)
+    const int nrun = (int)best.value.size();
+    const size_t fit = ((size_t)64 << 20) / (nvec * 3 * plane * sizeof(double2));
+    const int batch = (int)std::min<size_t>(std::min(nrun, 4 * 65535), std::max<size_t>(1, fit));
+    std::vector<int> tiles, tile0;  // {run in its batch, first direction, count}; first tile of each batch
+    for (int g = 0; g < nrun; ++g) {
+        if (g % batch == 0) tile0.push_back((int)tiles.size() / 3);
+        for (int d = best.start[g]; d < best.start[g + 1]; d += 64) {
+            tiles.push_back(g % batch);
+            tiles.push_back(d);
+            tiles.push_back(std::min(64, best.start[g + 1] - d));
+        }
+    }
+    tile0.push_back((int)tiles.size() / 3);
+    // rows per chunk: enough waves to fill the GPU a few times
+    const int64_t ntile = (int64_t)tiles.size() / 3;
+    const int rpc = (int)std::max<int64_t>(1, std::min<int64_t>(nv, (int64_t)nv * ntile * nvec / 4096));
+    const int nchunk = (nv + rpc - 1) / rpc;
+    const size_t npart = (size_t)nvec * nchunk * e3, nq = (size_t)nvec * batch * 3 * plane;
+    // host tables in one upload: the runs' values, the directions, the tiles
+    std::vector<double> tab((size_t)nrun + e3 + (tiles.size() + 1) / 2);
+    std::copy(best.value.begin(), best.value.end(), tab.begin());
+    std::copy(dirs, dirs + e3, tab.begin() + nrun);
+    std::memcpy(tab.data() + nrun + e3, tiles.data(), tiles.size() * sizeof(int));
+    if ((st = ensure_red(c, nq + npart + (size_t)nvec * e3 + tab.size() / 2 + 1)) != DDA_OK) return st;
+    double2 *Q = c.red, *part = Q + nq, *sums = part + npart;
+    double *dtab = (double *)(sums + (size_t)nvec * e3);
+    const int *dtiles = (const int *)(dtab + nrun + e3);
+    DDA_HIP_CHECK(hipMemcpyAsync(dtab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
+    for (size_t b = 0; b + 1 < tile0.size(); ++b) {
+        const int g0 = (int)b * batch, ng = std::min(batch, nrun - g0), t0 = tile0[b], nt = tile0[b + 1] - t0;
+        hipLaunchKernelGGL(k_ff_collapse, dim3((nu + 63) / 64 * nv, (ng + kFfGroups - 1) / kFfGroups, nvec), dim3(256), 0,
+                           c.stream, xa, xb, c.gmap, (int)c.N, nu, nv, n[a], stride[au], stride[av], stride[a],
+                           dtab + g0, ng, c.kd, Q);
+        hipLaunchKernelGGL(k_ff_plane, dim3(nt, nchunk, nvec), dim3(64), 0, c.stream, Q, nu, nv, ng, rpc,
+                           dtiles + 3 * (size_t)t0, dtab + nrun, au, av, ndir, c.kd, part);
+    }
+    hipLaunchKernelGGL(k_ff_sum, dim3((e3 + 63) / 64, nvec), dim3(512), 0, c.stream, part, e3, nchunk, sums);
     DDA_HIP_CHECK(hipGetLastError());
-    out.resize((size_t)ndir * 3);
     DDA_HIP_CHECK(hipMemcpyAsync(out.data(), sums, out.size() * sizeof(double2), hipMemcpyDeviceToHost, c.stream));
     DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
     return DDA_OK;
 }
 
 // F(n) = -i k^3 beta (I - n n) S
-static void finish_farfield(const Ctx &c, const dda_beam &bm, int ndir, const double *dirs,
-                            const std::vector<double2> &S, double *F) {
+static void finish_farfield(const Ctx &c, const dda_beam &bm, int ndir, const double *dirs, const double2 *S,
+                            double *F) {
     double br, bi;
     beta_of(c, bm, br, bi);
     const double k3 = c.kd * c.kd * c.kd;
@@ -362,9 +588,9 @@ dda_status dda_farfield(dda_ctx *h, const dda_beam *beam, const void *x, int32_t
         x = c->xtmp;
     }
     std::vector<double2> S;
-    st = farfield_sums(*c, (const double2 *)x, n_dir, dirs, S);
+    st = farfield_sums(*c, (const double2 *)x, nullptr, n_dir, dirs, S);
     if (st != DDA_OK) return st;
-    finish_farfield(*c, *beam, n_dir, dirs, S, F);
+    finish_farfield(*c, *beam, n_dir, dirs, S.data(), F);
     return DDA_OK;
 }
 
@@ -400,21 +626,25 @@ dda_status dda_asymmetry(dda_ctx *h, const dda_beam *beam, const void *x, int32_
     std::vector<double> mu, wmu;
     gauss_legendre(n_theta, mu, wmu);
     const int ndir = n_theta * n_phi;
-    std::vector<double> dirs((size_t)ndir * 3), wt(ndir), cs(ndir);
+    std::vector<double> dirs((size_t)ndir * 3), wt(ndir), cs(ndir), cph(n_phi), sph(n_phi);
+    for (int j = 0; j < n_phi; ++j) {
+        const double ph = 2.0 * M_PI * j / n_phi;
+        cph[j] = std::cos(ph);
+        sph[j] = std::sin(ph);
+    }
     for (int i = 0; i < n_theta; ++i)
         for (int j = 0; j < n_phi; ++j) {
-            const double ph = 2.0 * M_PI * j / n_phi, st = std::sqrt(std::max(0.0, 1.0 - mu[i] * mu[i]));
+            const double st = std::sqrt(std::max(0.0, 1.0 - mu[i] * mu[i]));
             const int d = i * n_phi + j;
-            for (int q = 0; q < 3; ++q)
-                dirs[3 * d + q] = mu[i] * a[q] + st * (std::cos(ph) * e1[q] + std::sin(ph) * e2[q]);
+            for (int q = 0; q < 3; ++q) dirs[3 * d + q] = mu[i] * a[q] + st * (cph[j] * e1[q] + sph[j] * e2[q]);
             wt[d] = wmu[i] * 2.0 * M_PI / n_phi;
             cs[d] = mu[i];
         }
     std::vector<double2> S;
-    dda_status st = farfield_sums(*c, (const double2 *)x, ndir, dirs.data(), S);
+    dda_status st = farfield_sums(*c, (const double2 *)x, nullptr, ndir, dirs.data(), S);
     if (st != DDA_OK) return st;
     std::vector<double> F((size_t)ndir * 6);
-    finish_farfield(*c, *beam, ndir, dirs.data(), S, F.data());
+    finish_farfield(*c, *beam, ndir, dirs.data(), S.data(), F.data());
     double csca = 0, gs = 0;
     const double k2 = c->kd * c->kd;
     for (int d = 0; d < ndir; ++d) {
@@ -478,13 +708,12 @@ dda_status dda_mueller(dda_ctx *h, const dda_beam *beam, const void *x1, const v
         x2 = P2;
     }
     std::vector<double2> S;
-    if ((st = farfield_sums(*c, (const double2 *)x1, n_theta, n.data(), S)) != DDA_OK) return st;
-    finish_farfield(*c, b, n_theta, n.data(), S, F1.data());
+    if ((st = farfield_sums(*c, (const double2 *)x1, (const double2 *)x2, n_theta, n.data(), S)) != DDA_OK) return st;
+    finish_farfield(*c, b, n_theta, n.data(), S.data(), F1.data());
     dda_beam b2 = b;
     for (int a = 0; a < 3; ++a) b2.pol_re[a] = e2[a];
     if (x2) {
-        if ((st = farfield_sums(*c, (const double2 *)x2, n_theta, n.data(), S)) != DDA_OK) return st;
-        finish_farfield(*c, b2, n_theta, n.data(), S, F2.data());
+        finish_farfield(*c, b2, n_theta, n.data(), S.data() + 3 * (size_t)n_theta, F2.data());
     } else {
         // F2(n) = R F1(R^T n), R the +90 degree rotation about e3 (takes e1 to e2); needs e3 = +-z
         if (!(std::fabs(std::fabs(e3[2]) - 1.0) < 1e-12) || !rot90_symmetric(*c)) {
@@ -501,8 +730,8 @@ dda_status dda_mueller(dda_ctx *h, const dda_beam *beam, const void *x1, const v
             nr[3 * i + 2] = vz;
         }
         std::vector<double> G(6 * (size_t)n_theta);
-        if ((st = farfield_sums(*c, (const double2 *)x1, n_theta, nr.data(), S)) != DDA_OK) return st;
-        finish_farfield(*c, b, n_theta, nr.data(), S, G.data());
+        if ((st = farfield_sums(*c, (const double2 *)x1, nullptr, n_theta, nr.data(), S)) != DDA_OK) return st;
+        finish_farfield(*c, b, n_theta, nr.data(), S.data(), G.data());
         for (int i = 0; i < n_theta; ++i)
             for (int part = 0; part < 2; ++part) {
                 const double gx = G[(3 * i) * 2 + part], gy = G[(3 * i + 1) * 2 + part], gz = G[(3 * i + 2) * 2 + part];
