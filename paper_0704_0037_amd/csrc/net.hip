@@ -74,73 +74,233 @@ union Frag {
 
 // ------------------------------------------------------------------ convolution (implicit GEMM)
 // out[m][n] = sum_{t, c} in[m + off_t][c] W[t][n][c] (+ bias[n] + skip[m][n], relu, x [y > 0]).
-// One wave computes 16 voxels x COUT channels: K runs over (tap, channel) in steps of 32, A rows
-// are voxels (8 consecutive channels of one shifted voxel per lane), B columns output channels.
+// K runs over (tap, channel) in steps of 32; the weights are the A operand (rows: 16 output channels)
+// and the shifted voxels the B operand (8 consecutive channels of one voxel per lane), so that a lane
+// ends with four consecutive channels of one voxel and stores them at once.
 // UP: the input lives on the half grid and is read at (z/2, y/2, x/2).
-template <int CIN, int COUT, bool UP>
-__global__ void __launch_bounds__(256) k_conv(const bf16 *__restrict__ in, const bf16 *__restrict__ W,
-                                              const float *__restrict__ bias, const bf16 *__restrict__ skip,
-                                              const bf16 *__restrict__ ymask, int relu, bf16 *__restrict__ out16,
-                                              float *__restrict__ out32, int out_stride, int out_valid, int g,
-                                              int nvox) {
-    constexpr int NT = COUT / 16;
-    constexpr int KCH = (27 * CIN + 31) / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = (blockIdx.x * 4 + wave) * 16;
-    if (m0 >= nvox) return;
-    const int ma = m0 + (lane & 15);  // this lane's A row (voxel)
-    const int kg = lane >> 4;
-    const bool mok = ma < nvox;
-    const int g3 = g * g * g;
-    const int b = ma / g3, r = ma % g3;
-    const int z = r / (g * g), y = (r / g) % g, x = r % g;
-    const int gi = UP ? g / 2 : g;
-    const size_t in_base = (size_t)b * gi * gi * gi;
-    f32x4 acc[NT];
+struct ConvArgs {
+    const bf16 *in, *W;
+    const float *bias;
+    const bf16 *skip, *ymask;
+    int relu;
+    bf16 *out16;
+    float *out32;
+    int out_stride, out_valid, g, nvox;
+};
+
+// channels co..co+3 of voxel m
+template <int COUT> __device__ __forceinline__ void conv_store(const ConvArgs &p, f32x4 acc, int m, int co) {
+    float v[4];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < KCH; ++kc) {
-        const int k0 = kc * 32 + kg * 8;
-        const int t = k0 / CIN, c0 = k0 % CIN;
-        Frag a;
-        a.u = make_uint4(0, 0, 0, 0);
-        if (t < 27 && mok) {
-            const int zz = z + t / 9 - 1, yy = y + (t / 3) % 3 - 1, xx = x + t % 3 - 1;
-            if (zz >= 0 && zz < g && yy >= 0 && yy < g && xx >= 0 && xx < g) {
-                const size_t v = UP ? in_base + ((size_t)(zz >> 1) * gi + (yy >> 1)) * gi + (xx >> 1)
-                                    : in_base + ((size_t)zz * g + yy) * g + xx;
-                a.u = *reinterpret_cast<const uint4 *>(in + v * CIN + c0);
-            }
-        }
+    for (int i = 0; i < 4; ++i) v[i] = acc[i];
+    if (p.bias) {
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            Frag w;
-            w.u = make_uint4(0, 0, 0, 0);
-            if (t < 27) w.u = *reinterpret_cast<const uint4 *>(W + ((size_t)t * COUT + n * 16 + (lane & 15)) * CIN + c0);
-            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, w.v, acc[n], 0, 0, 0);
-        }
+        for (int i = 0; i < 4; ++i) v[i] += p.bias[co + i];
     }
-    // D layout: lane holds rows 4*(lane/16) + i, column lane % 16 of each 16 x 16 tile
+    if (p.skip) {
+        const ushort4 q = *reinterpret_cast<const ushort4 *>(p.skip + (size_t)m * COUT + co);
+        v[0] += bf2f(q.x);
+        v[1] += bf2f(q.y);
+        v[2] += bf2f(q.z);
+        v[3] += bf2f(q.w);
+    }
+    if (p.relu) {
 #pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int co = n * 16 + (lane & 15);
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+    }
+    if (p.ymask) {
+        const ushort4 q = *reinterpret_cast<const ushort4 *>(p.ymask + (size_t)m * COUT + co);
+        if (!(bf2f(q.x) > 0.f)) v[0] = 0.f;
+        if (!(bf2f(q.y) > 0.f)) v[1] = 0.f;
+        if (!(bf2f(q.z) > 0.f)) v[2] = 0.f;
+        if (!(bf2f(q.w) > 0.f)) v[3] = 0.f;
+    }
+    if (p.out32) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = m0 + kg * 4 + i;
-            if (m >= nvox) continue;
-            float v = acc[n][i];
-            if (bias) v += bias[co];
-            if (skip) v += bf2f(skip[(size_t)m * COUT + co]);
-            if (relu) v = fmaxf(v, 0.f);
-            if (ymask && !(bf2f(ymask[(size_t)m * COUT + co]) > 0.f)) v = 0.f;
-            if (out32) {
-                if (co < out_valid) out32[(size_t)m * out_stride + co] = v;
-            } else {
-                out16[(size_t)m * COUT + co] = f2bf(v);
-            }
-        }
+        for (int i = 0; i < 4; ++i)
+            if (co + i < p.out_valid) p.out32[(size_t)m * p.out_stride + co + i] = v[i];
+    } else {
+        ushort4 q;
+        q.x = f2bf(v[0]);
+        q.y = f2bf(v[1]);
+        q.z = f2bf(v[2]);
+        q.w = f2bf(v[3]);
+        *reinterpret_cast<ushort4 *>(p.out16 + (size_t)m * COUT + co) = q;
     }
 }
+
+// Any grid: a wave takes 16 voxels x 16 output channels (blockIdx.y) and gathers its voxels through
+// the caches.  The coarse levels have few voxels, so the wave's chain of loads and products bounds
+// them: it loads the operands of kBatch steps before it multiplies, and the taps that leave the box
+// are masked, not branched around (one particle, 48 -> 64 channels on 6^3 voxels: 49 -> 7 us; one wave
+// took all output channels, one step at a time, before).
+constexpr int kBatch = 9;
+template <int CIN, int COUT, bool UP>
+__global__ void __launch_bounds__(256) k_conv(ConvArgs p) {
+    constexpr int KCH = (27 * CIN + 31) / 32;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m0 = (blockIdx.x * 4 + wave) * 16, n0 = blockIdx.y * 16;
+    if (m0 >= p.nvox) return;
+    const int m = m0 + (lane & 15), kg = lane >> 4, g = p.g;
+    const int ma = min(m, p.nvox - 1);
+    const int g3 = g * g * g, b = ma / g3, r = ma % g3;
+    const int pos[3] = {r / (g * g), (r / g) % g, r % g};  // z, y, x
+    const int gi = UP ? g / 2 : g;
+    // offsets of the three taps along each axis (channels), 0 where they leave the box
+    int off[3][3];
+    bool ok[3][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int q = pos[a] + d - 1;
+            ok[a][d] = m < p.nvox && q >= 0 && q < g;
+            off[a][d] = ok[a][d] ? (UP ? q >> 1 : q) * (a == 0 ? gi * gi : a == 1 ? gi : 1) * CIN : 0;
+        }
+    const bf16 *in = p.in + (size_t)b * gi * gi * gi * CIN;
+    const bf16 *w0 = p.W + (size_t)(n0 + (lane & 15)) * CIN;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k0 = 0; k0 < KCH; k0 += kBatch) {
+        Frag v[kBatch], w[kBatch];
+        bool vok[kBatch], wok[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (k0 + u >= KCH) continue;
+            // this lane's tap is ta, or ta + 1 from channel group `cut` of the step on
+            const int ka = (k0 + u) * 32, ta = ka / CIN, cut = ((ta + 1) * CIN - ka) / 8;
+            const bool hi = kg >= cut;
+            const int ca = ka + kg * 8 - (hi ? (ta + 1) * CIN : ta * CIN);
+            const int tb = ta + 1 < 27 ? ta + 1 : 26;
+            int o = off[0][ta / 9] + off[1][(ta / 3) % 3] + off[2][ta % 3];
+            bool in_box = ok[0][ta / 9] && ok[1][(ta / 3) % 3] && ok[2][ta % 3];
+            if (cut < 4) {
+                const int ob = off[0][tb / 9] + off[1][(tb / 3) % 3] + off[2][tb % 3];
+                const bool ib = ta + 1 < 27 && ok[0][tb / 9] && ok[1][(tb / 3) % 3] && ok[2][tb % 3];
+                o = hi ? ob : o;
+                in_box = hi ? ib : in_box;
+            }
+            vok[u] = in_box;
+            wok[u] = !hi || ta + 1 < 27;
+            v[u].u = *reinterpret_cast<const uint4 *>(in + o + ca);
+            w[u].u = *reinterpret_cast<const uint4 *>(w0 + (size_t)(hi ? tb : ta) * COUT * CIN + ca);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // all of the batch's loads before its products
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (k0 + u >= KCH) continue;
+            if (!vok[u]) v[u].u = make_uint4(0, 0, 0, 0);
+            if (!wok[u]) w[u].u = make_uint4(0, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u].v, v[u].v, acc, 0, 0, 0);
+        }
+    }
+    if (m < p.nvox) conv_store<COUT>(p, acc, m, n0 + kg * 4);
+}
+
+// Boxes whose side is a multiple of 8: a block takes four rows (y) of one particle and walks along z
+// with three planes of six rows in LDS (zero halo along x; rows and planes outside the box are staged
+// as zeros), the next plane's loads in flight while it multiplies.  The weights of all taps stay in
+// registers, so a product costs one LDS read; with 64 input channels they do not fit.  At 48^3,
+// batch 8: 16 -> 16 82 -> 37 us, 32 -> 16 up 167 -> 59 us, 16 -> 32 62 -> 30 us (the sums and their order
+// are those of k_conv, bit for bit).
+constexpr int kRowLoads = 6;  // staged 16-byte pieces per thread and plane
+// weight fragments a lane can hold (48 input channels fit, but one particle's 24^3 box then takes
+// 21 us instead of the gathering kernel's 9), and the output-channel tiles of one block (blockIdx.y: the
+// others)
+constexpr int conv_steps(int cin) { return (27 * cin + 31) / 32; }
+constexpr bool conv_rows_fits(int cin) { return conv_steps(cin) <= 27; }
+constexpr int conv_rows_tiles(int cin, int cout) { return conv_steps(cin) * (cout / 16) <= 28 ? cout / 16 : 1; }
+template <int CIN, int COUT, bool UP>
+__global__ void __launch_bounds__(256, 2) k_conv_rows(ConvArgs p, int zchunk) {
+    constexpr int NT = conv_rows_tiles(CIN, COUT), KCH = conv_steps(CIN), CG = CIN / 8;
+    const int n0 = blockIdx.y * NT * 16;
+    extern __shared__ __align__(16) unsigned char smem_conv[];
+    uint4 *lds = reinterpret_cast<uint4 *>(smem_conv);  // [3 planes][6 rows][g + 2][CG]
+    const int g = p.g, gi = UP ? g / 2 : g, t = threadIdx.x, lane = t & 63, wave = t >> 6, kg = lane >> 4;
+    const int rowp = (g + 2) * CG, planep = 6 * rowp;  // pitches in 16-byte pieces
+    int blk = blockIdx.x;
+    const int ytiles = g / 4, ztiles = (g + zchunk - 1) / zchunk;
+    const int y0 = (blk % ytiles) * 4;
+    blk /= ytiles;
+    const int z0 = (blk % ztiles) * zchunk, z1 = min(g, z0 + zchunk), b = blk / ztiles;
+    const bf16 *in = p.in + (size_t)b * gi * gi * gi * CIN;
+    // weights, tap-major (A rows: output channels)
+    Frag w[NT][KCH];
+#pragma unroll
+    for (int kc = 0; kc < KCH; ++kc) {
+        const int k = kc * 32 + kg * 8, tap = k / CIN, c = k % CIN;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            w[n][kc].u = make_uint4(0, 0, 0, 0);
+            if (tap < 27)
+                w[n][kc].u = *reinterpret_cast<const uint4 *>(p.W + ((size_t)tap * COUT + n0 + n * 16 + (lane & 15)) * CIN + c);
+        }
+    }
+    for (int e = t; e < 3 * planep; e += 256) lds[e] = make_uint4(0, 0, 0, 0);
+    const int pieces = 6 * g * CG;
+    uint4 st[kRowLoads];
+    auto fetch = [&](int z) {  // plane z, rows y0 - 1 .. y0 + 4
+#pragma unroll
+        for (int i = 0; i < kRowLoads; ++i) {
+            const int e = t + i * 256, row = e / (g * CG), q = e % (g * CG), x = q / CG, y = y0 - 1 + row;
+            st[i] = make_uint4(0, 0, 0, 0);
+            if (e < pieces && z >= 0 && z < g && y >= 0 && y < g)
+                st[i] = *reinterpret_cast<const uint4 *>(
+                    in + ((size_t)((UP ? z >> 1 : z) * gi + (UP ? y >> 1 : y)) * gi + (UP ? x >> 1 : x)) * CIN + (q % CG) * 8);
+        }
+    };
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < kRowLoads; ++i) {
+            const int e = t + i * 256, row = e / (g * CG), q = e % (g * CG);
+            if (e < pieces) lds[slot * planep + row * rowp + CG + q] = st[i];
+        }
+    };
+    __syncthreads();
+    fetch(z0 - 1);
+    put(0);
+    fetch(z0);
+    put(1);
+    fetch(z0 + 1);
+    const int tiles = g / 4;  // of 2 rows x 8 voxels: two row pairs x g / 8
+    const int lv = (lane >> 3) & 1, lx = lane & 7;
+    for (int z = z0; z < z1; ++z) {
+        const int s0 = (z - z0) % 3;  // slots of planes z - 1, z, z + 1
+        const int slot[3] = {s0, s0 == 2 ? 0 : s0 + 1, s0 == 0 ? 2 : s0 - 1};
+        put(slot[2]);
+        __syncthreads();
+        if (z + 1 < z1) fetch(z + 2);
+        for (int tl = wave; tl < tiles; tl += 4) {
+            const int yy = (tl & 1) * 2 + lv, x = (tl >> 1) * 8 + lx;
+            const int base = yy * rowp + x * CG;  // tap (dy, dx) = (-1, -1): the halo shifts rows and voxels by one
+            f32x4 acc[NT];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kc = 0; kc < KCH; ++kc) {
+                // taps of the step: ta, or ta + 1 from channel group `cut` on
+                const int ka = kc * 32, ta = ka / CIN, cut = ((ta + 1) * CIN - ka) / 8, tb = ta + 1 < 27 ? ta + 1 : 26;
+                const int oa = slot[ta / 9] * planep + ((ta / 3) % 3) * rowp + (ta % 3) * CG + (ka - ta * CIN) / 8;
+                int o = oa;
+                if (cut < 4) {
+                    const int ob = slot[tb / 9] * planep + ((tb / 3) % 3) * rowp + (tb % 3) * CG - cut;
+                    o = kg >= cut ? ob : oa;
+                }
+                Frag v;
+                v.u = lds[base + o + kg];
+                if (ta + 1 >= 27 && cut < 4 && kg >= cut) v.u = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+                    acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[n][kc].v, v.v, acc[n], 0, 0, 0);
+            }
+            const int m = ((b * g + z) * g + y0 + yy) * g + x;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) conv_store<COUT>(p, acc[n], m, n0 + n * 16 + kg * 4);
+        }
+        __syncthreads();
+    }
+}
+inline size_t conv_rows_lds(int g, int cin) { return (size_t)3 * 6 * (g + 2) * cin * sizeof(bf16); }
 
 // ------------------------------------------------------------------ weight gradient
 // part[blk][t][co][ci] = sum over the block's voxels m of g[m][co] in[m + off_t][ci], tap t =
@@ -224,73 +384,248 @@ __global__ void __launch_bounds__(256) k_wgrad(const bf16 *__restrict__ gr, cons
     if (t == 13 && threadIdx.x < COUT) bpart[(size_t)blockIdx.x * COUT + threadIdx.x] = bsum;
 }
 
-// canonical gradient of one layer = the sum of the block partials (fixed order), real channels only
-__global__ void k_wgrad_reduce(const float *__restrict__ part, const float *__restrict__ bpart, int nblk, int pco,
-                               int pci, int co_r, int ci_r, float *__restrict__ gw, float *__restrict__ gb) {
-    const int nw = 27 * co_r * ci_r;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// Weight gradient on boxes whose side is a multiple of 8: a block takes four rows (y) of one particle,
+// 16 output and 16 input channels (blockIdx.y), and walks along z; the planes z - 1 .. z + 1 of the
+// input (six rows, zero halo) and the plane z of the gradient sit in LDS as [row][channel][x], so the
+// products of all 27 taps read what was staged once.  A step is 4 rows x 8 voxels; wave dz takes the
+// nine taps of plane z + dz - 1, the shifts by one voxel are formed from one 16-byte read and its
+// neighbour words.  Bound by the staging (every voxel transposed with two-byte granularity); at 48^3,
+// batch 8, 16 x 16 channels 389 -> 30 us, 32 -> 16 up 494 -> 60 us (one tap per block before, which staged
+// gradient and input 27 times; 42 and 75 us without the next planes' loads in flight).
+template <int CIN, int COUT, bool UP>
+__global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr, const bf16 *__restrict__ in, int g,
+                                                    int zchunk, float *__restrict__ part, float *__restrict__ bpart) {
+    extern __shared__ __align__(16) unsigned char smem_wg[];
+    const int t = threadIdx.x, lane = t & 63, dz = t >> 6, kg = lane >> 4, ch = lane & 15;
+    const int ci0 = (blockIdx.y % (CIN / 16)) * 16, co0 = (blockIdx.y / (CIN / 16)) * 16;
+    const int gi = UP ? g / 2 : g;
+    const int xp = g + 24;             // pitch of one channel's row: 8 before, the voxels, 16 after (16-byte rows, skewed banks)
+    const int rowp = 16 * xp;          // one row of 16 channels
+    bf16 *xs = reinterpret_cast<bf16 *>(smem_wg);  // [3][6][16][xp]
+    bf16 *gs = xs + 18 * rowp;                     // [4][16][xp]
+    int blk = blockIdx.x;
+    const int ytiles = g / 4, ztiles = (g + zchunk - 1) / zchunk;
+    const int y0 = (blk % ytiles) * 4;
+    blk /= ytiles;
+    const int z0 = (blk % ztiles) * zchunk, z1 = min(g, z0 + zchunk), b = blk / ztiles;
+    const bf16 *inb = in + (size_t)b * gi * gi * gi * CIN + ci0;
+    const bf16 *grb = gr + (size_t)b * g * g * g * COUT + co0;
+    for (int e = t; e < 22 * rowp / 8; e += 192) reinterpret_cast<uint4 *>(xs)[e] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    // two neighbouring voxels' eight channels -> eight words [channel][x, x + 1]
+    auto put = [&](bf16 *dst, int x, const Frag &a, const Frag &c) {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(&a.u), *q = reinterpret_cast<const uint32_t *>(&c.u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            *reinterpret_cast<uint32_t *>(dst + (2 * k) * xp + 8 + x) = (p[k] & 0xFFFFu) | (q[k] << 16);
+            *reinterpret_cast<uint32_t *>(dst + (2 * k + 1) * xp + 8 + x) = (p[k] >> 16) | (q[k] & 0xFFFF0000u);
+        }
+    };
+    const int half = g / 2;
+    Frag xa[2], xc[2], ga[2], gc[2];  // staged pairs of voxels (at most two per thread: g <= 64)
+    auto fetch_in = [&](int z) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = t + i * 192, x = (e % half) * 2, hc = (e / half) & 1, row = e / (2 * half), y = y0 - 1 + row;
+            xa[i].u = xc[i].u = make_uint4(0, 0, 0, 0);
+            if (e < 12 * half && z >= 0 && z < g && y >= 0 && y < g) {
+                const bf16 *s = inb + ((size_t)((UP ? z >> 1 : z) * gi + (UP ? y >> 1 : y)) * gi + (UP ? x >> 1 : x)) * CIN + hc * 8;
+                xa[i].u = *reinterpret_cast<const uint4 *>(s);
+                xc[i].u = UP ? xa[i].u : *reinterpret_cast<const uint4 *>(s + CIN);
+            }
+        }
+    };
+    auto put_in = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = t + i * 192, x = (e % half) * 2, hc = (e / half) & 1, row = e / (2 * half);
+            if (e < 12 * half) put(xs + (slot * 6 + row) * rowp + hc * 8 * xp, x, xa[i], xc[i]);
+        }
+    };
+    auto fetch_g = [&](int z) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = t + i * 192, x = (e % half) * 2, hc = (e / half) & 1, row = e / (2 * half);
+            if (e < 8 * half) {
+                const bf16 *s = grb + ((size_t)(z * g + y0 + row) * g + x) * COUT + hc * 8;
+                ga[i].u = *reinterpret_cast<const uint4 *>(s);
+                gc[i].u = *reinterpret_cast<const uint4 *>(s + COUT);
+            }
+        }
+    };
+    auto put_g = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = t + i * 192, x = (e % half) * 2, hc = (e / half) & 1, row = e / (2 * half);
+            if (e < 8 * half) put(gs + row * rowp + hc * 8 * xp, x, ga[i], gc[i]);
+        }
+    };
+    f32x4 acc[9], bacc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Frag ones;
+    ones.u = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+    fetch_in(z0 - 1);
+    put_in(0);
+    fetch_in(z0);
+    put_in(1);
+    fetch_in(z0 + 1);
+    fetch_g(z0);
+    for (int z = z0; z < z1; ++z) {
+        const int s0 = (z - z0) % 3, slot2 = s0 == 0 ? 2 : s0 - 1;
+        put_in(slot2);
+        put_g();
+        __syncthreads();
+        if (z + 1 < z1) {  // the next planes on their way during the products
+            fetch_in(z + 2);
+            fetch_g(z + 1);
+        }
+        const int sl = (s0 + dz) % 3;
+        const bf16 *xrow = xs + (sl * 6 + kg) * rowp + ch * xp;  // row of tap dy = -1
+        const bf16 *grow = gs + kg * rowp + ch * xp;
+        for (int x = 0; x < g; x += 8) {
+            Frag a;
+            a.u = *reinterpret_cast<const uint4 *>(grow + 8 + x);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const bf16 *r = xrow + dy * rowp + 8 + x;
+                Frag c, l, h;
+                c.u = *reinterpret_cast<const uint4 *>(r);
+                const uint32_t pv = *reinterpret_cast<const uint32_t *>(r - 2), nx = *reinterpret_cast<const uint32_t *>(r + 8);
+                const uint32_t m1 = __builtin_amdgcn_alignbit(c.u.y, c.u.x, 16), m2 = __builtin_amdgcn_alignbit(c.u.z, c.u.y, 16),
+                               m3 = __builtin_amdgcn_alignbit(c.u.w, c.u.z, 16);
+                l.u = make_uint4(__builtin_amdgcn_alignbit(c.u.x, pv, 16), m1, m2, m3);  // voxels x - 1 .. x + 6
+                h.u = make_uint4(m1, m2, m3, __builtin_amdgcn_alignbit(nx, c.u.w, 16));  // voxels x + 1 .. x + 8
+                acc[3 * dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, l.v, acc[3 * dy], 0, 0, 0);
+                acc[3 * dy + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, c.v, acc[3 * dy + 1], 0, 0, 0);
+                acc[3 * dy + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, h.v, acc[3 * dy + 2], 0, 0, 0);
+            }
+            if (dz == 1 && ci0 == 0) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, bacc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // D: rows (output channels) 4 kg + i, column (input channel) lane & 15
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        float *dst = part + (((size_t)blockIdx.x * 27 + dz * 9 + k) * COUT + co0) * CIN + ci0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[(size_t)(kg * 4 + i) * CIN + ch] = acc[k][i];
+    }
+    if (dz == 1 && ci0 == 0 && ch == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bpart[(size_t)blockIdx.x * COUT + co0 + kg * 4 + i] = bacc[i];
+}
+inline size_t wgrad_rows_lds(int g) { return (size_t)22 * 16 * (g + 24) * sizeof(bf16); }
+
+// canonical gradient of one layer = the sum of the block partials in a fixed order (a block: 64
+// entries, 8 strided partial sums each), real channels only
+__global__ void __launch_bounds__(512) k_wgrad_reduce(const float *__restrict__ part, const float *__restrict__ bpart,
+                                                      int nblk, int pco, int pci, int co_r, int ci_r,
+                                                      float *__restrict__ gw, float *__restrict__ gb) {
+    __shared__ float sh[8][64];
+    const int nw = 27 * co_r * ci_r, lx = threadIdx.x & 63, ly = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lx;
+    const float *src = nullptr;
+    size_t stride = 0;
     if (e < nw) {
         const int t = e / (co_r * ci_r), co = (e / ci_r) % co_r, ci = e % ci_r;
-        const size_t src = ((size_t)t * pco + co) * pci + ci, stride = (size_t)27 * pco * pci;
-        float s = 0.f;
-        for (int b = 0; b < nblk; ++b) s += part[b * stride + src];
-        gw[e] = s;
+        src = part + ((size_t)t * pco + co) * pci + ci;
+        stride = (size_t)27 * pco * pci;
     } else if (e < nw + co_r) {
-        const int co = e - nw;
-        float s = 0.f;
-        for (int b = 0; b < nblk; ++b) s += bpart[(size_t)b * pco + co];
-        gb[co] = s;
+        src = bpart + (e - nw);
+        stride = pco;
+    }
+    float s = 0.f;
+    if (src) {
+        int b = ly;
+        for (; b + 24 < nblk; b += 32) {  // four loads in flight
+            const float q0 = src[b * stride], q1 = src[(b + 8) * stride], q2 = src[(b + 16) * stride], q3 = src[(b + 24) * stride];
+            s += (q0 + q1) + (q2 + q3);
+        }
+        for (; b < nblk; b += 8) s += src[b * stride];
+    }
+    sh[ly][lx] = s;
+    __syncthreads();
+    if (ly == 0 && src) {
+        for (int k = 1; k < 8; ++k) s += sh[k][lx];
+        (e < nw ? gw[e] : gb[e - nw]) = s;
     }
 }
 
 // ------------------------------------------------------------------ pooling and its adjoints
-__global__ void k_pool(const bf16 *__restrict__ in, bf16 *__restrict__ out, int go, int C, int nvo) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nvo * C) return;
-    const int c = e % C, m = e / C;
-    const int g3 = go * go * go, b = m / g3, r = m % g3;
-    const int z = r / (go * go), y = (r / go) % go, x = r % go;
-    const int gi = 2 * go;
-    float s = 0.f;
+// One thread per eight channels of a voxel (16-byte accesses): bound by memory.
+__device__ __forceinline__ void unpack8(const bf16 *p, float (&v)[8]) {
+    Frag f;
+    f.u = *reinterpret_cast<const uint4 *>(p);
+    const bf16 *h = reinterpret_cast<const bf16 *>(&f.u);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = bf2f(h[i]);
+}
+__device__ __forceinline__ void pack8(bf16 *p, const float (&v)[8]) {
+    Frag f;
+    bf16 *h = reinterpret_cast<bf16 *>(&f.u);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = f2bf(v[i]);
+    *reinterpret_cast<uint4 *>(p) = f.u;
+}
+// sum over the eight children (in the order z, y, x) of voxel m of a grid of side g
+__device__ __forceinline__ void sum_children(const bf16 *in, int m, int c8, int g, int C, float (&s)[8]) {
+    const int g3 = g * g * g, b = m / g3, r = m % g3, gf = 2 * g;
+    const int z = r / (g * g), y = (r / g) % g, x = r % g;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = 0.f;
+#pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const size_t v = (size_t)b * gi * gi * gi + ((size_t)(2 * z + (q >> 2)) * gi + 2 * y + ((q >> 1) & 1)) * gi +
+        const size_t v = (size_t)b * gf * gf * gf + ((size_t)(2 * z + (q >> 2)) * gf + 2 * y + ((q >> 1) & 1)) * gf +
                          2 * x + (q & 1);
-        s += bf2f(in[v * C + c]);
+        float t[8];
+        unpack8(in + v * C + c8, t);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[i] += t[i];
     }
-    out[e] = f2bf(s * 0.125f);
+}
+__global__ void k_pool(const bf16 *__restrict__ in, bf16 *__restrict__ out, int go, int C, int nvo) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, cg = C / 8;
+    if (e >= nvo * cg) return;
+    const int c8 = e % cg * 8, m = e / cg;
+    float s[8];
+    sum_children(in, m, c8, go, C, s);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] *= 0.125f;
+    pack8(out + (size_t)m * C + c8, s);
 }
 
 // g[parent] = (sum of the 8 children of gf) x [y > 0]  (adjoint of up, then relu mask)
 __global__ void k_up_adj_mask(const bf16 *__restrict__ gf, const bf16 *__restrict__ y, bf16 *__restrict__ g, int gc,
                               int C, int nvc) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nvc * C) return;
-    const int c = e % C, m = e / C;
-    const int g3 = gc * gc * gc, b = m / g3, r = m % g3;
-    const int z = r / (gc * gc), yy = (r / gc) % gc, x = r % gc;
-    const int gf3 = 8 * g3, gfs = 2 * gc;
-    float s = 0.f;
-    for (int q = 0; q < 8; ++q) {
-        const size_t v = (size_t)b * gf3 + ((size_t)(2 * z + (q >> 2)) * gfs + 2 * yy + ((q >> 1) & 1)) * gfs + 2 * x + (q & 1);
-        s += bf2f(gf[v * C + c]);
-    }
-    const bf16 h = f2bf(s);
-    g[e] = bf2f(y[e]) > 0.f ? h : (bf16)0;
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, cg = C / 8;
+    if (e >= nvc * cg) return;
+    const int c8 = e % cg * 8, m = e / cg;
+    float s[8], yv[8];
+    sum_children(gf, m, c8, gc, C, s);
+    unpack8(y + (size_t)m * C + c8, yv);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = yv[i] > 0.f ? s[i] : 0.f;
+    pack8(g + (size_t)m * C + c8, s);
 }
 
 // g[child] = (gskip[child] + gp[parent] / 8) x [y > 0]  (adjoint of pool plus the skip path)
 __global__ void k_pool_adj_add_mask(const bf16 *__restrict__ gp, const bf16 *__restrict__ gskip,
                                     const bf16 *__restrict__ y, bf16 *__restrict__ g, int gf, int C, int nvf) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nvf * C) return;
-    const int c = e % C, m = e / C;
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, cg = C / 8;
+    if (e >= nvf * cg) return;
+    const int c8 = e % cg * 8, m = e / cg;
     const int g3 = gf * gf * gf, b = m / g3, r = m % g3;
     const int z = r / (gf * gf), yy = (r / gf) % gf, x = r % gf;
     const int gc = gf / 2;
     const size_t par = (size_t)b * gc * gc * gc + ((size_t)(z >> 1) * gc + (yy >> 1)) * gc + (x >> 1);
-    const float s = bf2f(gskip[e]) + 0.125f * bf2f(gp[par * C + c]);
-    const bf16 h = f2bf(s);
-    g[e] = bf2f(y[e]) > 0.f ? h : (bf16)0;
+    float s[8], p[8], yv[8];
+    unpack8(gskip + (size_t)m * C + c8, s);
+    unpack8(gp + par * C + c8, p);
+    unpack8(y + (size_t)m * C + c8, yv);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = yv[i] > 0.f ? s[i] + 0.125f * p[i] : 0.f;
+    pack8(g + (size_t)m * C + c8, s);
 }
 
 // ------------------------------------------------------------------ loss
@@ -327,27 +662,47 @@ __global__ void __launch_bounds__(kLossThreads) k_loss_part(const float *__restr
     }
 }
 
-__global__ void k_loss_fin(const double *__restrict__ part, int nb, double *__restrict__ res) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double a = 0, n = 0;
-    for (int b = 0; b < nb; ++b) {
-        a += part[2 * b];
-        n += part[2 * b + 1];
+// one block of kLossBlocks threads, tree order
+__global__ void __launch_bounds__(kLossThreads) k_loss_fin(const double *__restrict__ part, int nb,
+                                                           double *__restrict__ res) {
+    __shared__ double s0[kLossThreads], s1[kLossThreads];
+    const int t = threadIdx.x;
+    s0[t] = t < nb ? part[2 * t] : 0.0;
+    s1[t] = t < nb ? part[2 * t + 1] : 0.0;
+    __syncthreads();
+    for (int h = kLossThreads / 2; h > 0; h >>= 1) {
+        if (t < h) {
+            s0[t] += s0[t + h];
+            s1[t] += s1[t + h];
+        }
+        __syncthreads();
     }
-    res[0] = n > 0 ? a / n : 0.0;
-    res[1] = n;
+    if (t == 0) {
+        res[0] = s1[0] > 0 ? s0[0] / s1[0] : 0.0;
+        res[1] = s1[0];
+    }
 }
 
 // gradient of the loss w.r.t. the output, bf16 [nvox][16] (padded channels zero)
 __global__ void k_out_grad(const float *__restrict__ out, const float *__restrict__ tgt, const bf16 *__restrict__ feat,
                            int nvox, const double *__restrict__ res, bf16 *__restrict__ g) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nvox * 16) return;
-    const int m = e / 16, c = e % 16;
-    float v = 0.f;
-    if (c < kOut && bf2f(feat[(size_t)m * 16]) > 0.f && res[1] > 0)
-        v = (float)(2.0 * ((double)out[(size_t)m * kOut + c] - (double)tgt[(size_t)m * kOut + c]) / res[1]);
-    g[e] = f2bf(v);
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= nvox) return;
+    float v[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = 0.f;
+    const double n = res[1];
+    if (bf2f(feat[(size_t)m * 16]) > 0.f && n > 0)
+#pragma unroll
+        for (int c = 0; c < kOut; ++c)
+            v[c] = (float)(2.0 * ((double)out[(size_t)m * kOut + c] - (double)tgt[(size_t)m * kOut + c]) / n);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float q[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = v[8 * h + i];
+        pack8(g + (size_t)m * 16 + 8 * h, q);
+    }
 }
 
 // ------------------------------------------------------------------ optimizer and weight copies
@@ -530,20 +885,32 @@ static dda_status refresh(Net &n) {
     return DDA_OK;
 }
 
-// one convolution launch; (cin, cout, up) picks the instantiation
+// one convolution launch; (cin, cout, up) picks the instantiation.  k_conv_rows where the weights fit
+// its registers, the box its tiles and the staged planes a quarter of a compute unit's LDS per block
+template <int CI, int CO, bool UPM> static bool conv_launch(const ConvArgs &p, hipStream_t s) {
+    if constexpr (conv_rows_fits(CI)) {
+        const size_t lds = conv_rows_lds(p.g, CI);
+        if (p.g % 8 == 0 && 6 * p.g * (CI / 8) <= kRowLoads * 256 && lds <= 64 * 1024) {
+            // z chunks: about four blocks per compute unit, at least two planes each
+            const int batch = p.nvox / (p.g * p.g * p.g), ytiles = p.g / 4, ny = CO / 16 / conv_rows_tiles(CI, CO);
+            const int zt = std::max(1, std::min(p.g / 2, 1024 / std::max(1, batch * ytiles * ny)));
+            const int zc = (p.g + zt - 1) / zt;
+            hipLaunchKernelGGL((k_conv_rows<CI, CO, UPM>), dim3(batch * ytiles * ((p.g + zc - 1) / zc), ny), dim3(256),
+                               lds, s, p, zc);
+            return true;
+        }
+    }
+    hipLaunchKernelGGL((k_conv<CI, CO, UPM>), dim3((unsigned)((p.nvox + 63) / 64), CO / 16), dim3(256), 0, s, p);
+    return true;
+}
+
 static dda_status conv(Net &n, int cin, int cout, bool upm, const bf16 *in, const bf16 *W, const float *bias,
                        const bf16 *skip, const bf16 *ymask, int relu, bf16 *o16, float *o32, int ostride, int ovalid,
                        int g, size_t nv) {
-    const dim3 grid((unsigned)((nv + 63) / 64)), blk(256);
-    hipStream_t s = n.stream;
-    const int nvi = (int)nv;
-#define DNET_CONV(CI, CO, UPM)                                                                                  \
-    if (cin == CI && cout == CO && upm == UPM) {                                                                \
-        hipLaunchKernelGGL((k_conv<CI, CO, UPM>), grid, blk, 0, s, in, W, bias, skip, ymask, relu, o16, o32,    \
-                           ostride, ovalid, g, nvi);                                                            \
-        DNET_CHECK(hipGetLastError());                                                                          \
-        return DDA_OK;                                                                                          \
-    }
+    const ConvArgs p{in, W, bias, skip, ymask, relu, o16, o32, ostride, ovalid, g, (int)nv};
+    bool done = false;
+#define DNET_CONV(CI, CO, UPM) \
+    if (!done && cin == CI && cout == CO && upm == UPM) done = conv_launch<CI, CO, UPM>(p, n.stream);
     DNET_CONV(16, 16, false)
     DNET_CONV(16, 32, false)
     DNET_CONV(32, 48, false)
@@ -555,26 +922,57 @@ static dda_status conv(Net &n, int cin, int cout, bool upm, const bf16 *in, cons
     DNET_CONV(48, 32, false)
     DNET_CONV(64, 48, false)
 #undef DNET_CONV
-    set_error("dda_net: no convolution instantiated for these channels");
-    return DDA_ENOTSUP;
+    if (!done) {
+        set_error("dda_net: no convolution instantiated for these channels");
+        return DDA_ENOTSUP;
+    }
+    DNET_CHECK(hipGetLastError());
+    return DDA_OK;
+}
+
+// blocks of a layer's weight gradient: rows of four and z chunks where k_wgrad_rows takes the box
+// (about two blocks per compute unit over all channel tiles), else chunks of voxels
+struct WgradShape {
+    bool rows;
+    int chunk, nblk;
+};
+static WgradShape wgrad_shape(const LayerDef &d, int g, int batch) {
+    WgradShape w;
+    w.rows = g % 8 == 0 && g <= 64;  // two staged pairs per thread, 62 KB of LDS
+    const size_t nv = (size_t)batch * g * g * g;
+    if (w.rows) {
+        const int per_z = batch * (g / 4), pairs = d.pcin / 16 * (d.pcout / 16);
+        const int zt = std::max(1, std::min(g / 4, 512 / std::max(1, per_z * pairs)));
+        w.chunk = (g + zt - 1) / zt;
+        w.nblk = per_z * ((g + w.chunk - 1) / w.chunk);
+    } else {
+        w.chunk = chunk_of(nv);
+        w.nblk = (int)((nv + w.chunk - 1) / w.chunk);
+    }
+    return w;
 }
 
 static dda_status wgrad(Net &n, int l, const bf16 *g, const bf16 *in, int gside, size_t nv) {
     const LayerDef &d = kDefs[l];
-    const int chunk = chunk_of(nv);
-    const int nblk = (int)((nv + chunk - 1) / chunk);
-    if ((size_t)nblk * 27 * d.pcout * d.pcin > n.part_elems || (size_t)nblk * d.pcout > n.bpart_elems) {
+    const WgradShape w = wgrad_shape(d, gside, (int)(nv / ((size_t)gside * gside * gside)));
+    if ((size_t)w.nblk * 27 * d.pcout * d.pcin > n.part_elems || (size_t)w.nblk * d.pcout > n.bpart_elems) {
         set_error("dda_net: gradient partial buffer too small");
         return DDA_EINVAL;
     }
-    const dim3 grid(nblk, 27), blk(256);
     hipStream_t s = n.stream;
     const int nvi = (int)nv;
+    const dim3 rgrid(w.nblk, d.pcin / 16 * (d.pcout / 16));
+    const size_t lds = wgrad_rows_lds(gside);
     bool done = false;
-#define DNET_WG(CI, CO, UPM)                                                                                     \
-    if (!done && d.pcin == CI && d.pcout == CO && (d.kind == 2) == UPM) {                                        \
-        hipLaunchKernelGGL((k_wgrad<CI, CO, UPM>), grid, blk, 0, s, g, in, gside, nvi, chunk, n.part, n.bpart); \
-        done = true;                                                                                             \
+#define DNET_WG(CI, CO, UPM)                                                                                        \
+    if (!done && d.pcin == CI && d.pcout == CO && (d.kind == 2) == UPM) {                                           \
+        if (w.rows)                                                                                                 \
+            hipLaunchKernelGGL((k_wgrad_rows<CI, CO, UPM>), rgrid, dim3(192), lds, s, g, in, gside, w.chunk, n.part, \
+                               n.bpart);                                                                            \
+        else                                                                                                        \
+            hipLaunchKernelGGL((k_wgrad<CI, CO, UPM>), dim3(w.nblk, 27), dim3(256), 0, s, g, in, gside, nvi, w.chunk, \
+                               n.part, n.bpart);                                                                    \
+        done = true;                                                                                                \
     }
     DNET_WG(16, 16, false)
     DNET_WG(16, 32, false)
@@ -589,8 +987,8 @@ static dda_status wgrad(Net &n, int l, const bf16 *g, const bf16 *in, int gside,
         return DDA_ENOTSUP;
     }
     const int tot = 27 * d.cout * d.cin + d.cout;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((tot + 255) / 256), dim3(256), 0, s, n.part, n.bpart, nblk, d.pcout,
-                       d.pcin, d.cout, d.cin, n.grad + n.off_w[l], n.grad + n.off_b[l]);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((tot + 63) / 64), dim3(512), 0, s, n.part, n.bpart, w.nblk, d.pcout, d.pcin,
+                       d.cout, d.cin, n.grad + n.off_w[l], n.grad + n.off_b[l]);
     DNET_CHECK(hipGetLastError());
     return DDA_OK;
 }
@@ -605,7 +1003,7 @@ static dda_status forward(Net &n, const bf16 *feat, int B) {
     for (int l = 1; l <= 3; ++l) {
         const LayerDef &d = kDefs[l];
         const size_t nv = vox(n, l, B);
-        hipLaunchKernelGGL(k_pool, dim3((unsigned)((nv * d.pcin + 255) / 256)), dim3(256), 0, n.stream, n.e[l - 1],
+        hipLaunchKernelGGL(k_pool, dim3((unsigned)((nv * (d.pcin / 8) + 255) / 256)), dim3(256), 0, n.stream, n.e[l - 1],
                            n.p[l - 1], side(n, l), d.pcin, (int)nv);
         if ((st = conv(n, d.pcin, d.pcout, false, n.p[l - 1], n.W[l], n.bias[l], nullptr, nullptr, 1, n.e[l], nullptr,
                        0, 0, side(n, l), nv)) != DDA_OK)
@@ -632,8 +1030,9 @@ static dda_status backward(Net &n, const bf16 *feat, const float *tgt, int B) {
     const int G = n.G;
     const size_t nv0 = vox(n, 0, B);
     hipLaunchKernelGGL(k_loss_part, dim3(kLossBlocks), dim3(kLossThreads), 0, s, n.out, tgt, feat, (int)nv0, n.lpart);
-    hipLaunchKernelGGL(k_loss_fin, dim3(1), dim3(64), 0, s, n.lpart, kLossBlocks, n.lres);
-    hipLaunchKernelGGL(k_out_grad, dim3((unsigned)((nv0 * 16 + 255) / 256)), dim3(256), 0, s, n.out, tgt, feat,
+    static_assert(kLossBlocks <= kLossThreads, "k_loss_fin takes one partial per thread");
+    hipLaunchKernelGGL(k_loss_fin, dim3(1), dim3(kLossThreads), 0, s, n.lpart, kLossBlocks, n.lres);
+    hipLaunchKernelGGL(k_out_grad, dim3((unsigned)((nv0 + 255) / 256)), dim3(256), 0, s, n.out, tgt, feat,
                        (int)nv0, n.lres, n.gout);
     DNET_CHECK(hipGetLastError());
     // gl[l]: gradient at the pre-activation of layer l (relu mask applied)
@@ -654,7 +1053,7 @@ static dda_status backward(Net &n, const bf16 *feat, const float *tgt, int B) {
                        0, side(n, lev), nv)) != DDA_OK)
             return st;
         const bf16 *ycoarse = l == 4 ? n.e[3] : n.d[lev + 1];
-        hipLaunchKernelGGL(k_up_adj_mask, dim3((unsigned)((nvc * d.pcin + 255) / 256)), dim3(256), 0, s, n.gtmp,
+        hipLaunchKernelGGL(k_up_adj_mask, dim3((unsigned)((nvc * (d.pcin / 8) + 255) / 256)), dim3(256), 0, s, n.gtmp,
                            ycoarse, n.gl[l - 1], side(n, lev + 1), d.pcin, (int)nvc);
     }
     // encoder layers 3, 2, 1: input pool(e2), pool(e1), pool(e0); e_l also feeds the skip of layer 6 - l... (l-1 level)
@@ -668,7 +1067,7 @@ static dda_status backward(Net &n, const bf16 *feat, const float *tgt, int B) {
             return st;
         // e_{lev-1} is the skip input of the decoder layer on level lev-1: layer 7 - lev
         const bf16 *gskip = n.gl[7 - lev];
-        hipLaunchKernelGGL(k_pool_adj_add_mask, dim3((unsigned)((nvf * d.pcin + 255) / 256)), dim3(256), 0, s, n.gtmp,
+        hipLaunchKernelGGL(k_pool_adj_add_mask, dim3((unsigned)((nvf * (d.pcin / 8) + 255) / 256)), dim3(256), 0, s, n.gtmp,
                            gskip, n.e[lev - 1], n.gl[l - 1], side(n, lev - 1), d.pcin, (int)nvf);
     }
     if ((st = wgrad(n, 0, n.gl[0], feat, G, nv0)) != DDA_OK) return st;
@@ -745,7 +1144,9 @@ dda_status dda_net_create(dda_net **out, int32_t grid, int32_t max_batch, const 
     for (int l = 0; l < kLayers; ++l) {
         const size_t nv = vox(*n, kDefs[l].level, B);
         gt = std::max(gt, nv * kDefs[l].pcin);
-        const size_t nblk = (nv + chunk_of(nv) - 1) / chunk_of(nv);
+        // fewer particles than B can mean more blocks (smaller chunks along z)
+        size_t nblk = 0;
+        for (int q = 1; q <= B; ++q) nblk = std::max(nblk, (size_t)wgrad_shape(kDefs[l], side(*n, kDefs[l].level), q).nblk);
         pe = std::max(pe, nblk * 27 * kDefs[l].pcin * kDefs[l].pcout);
         be = std::max(be, nblk * kDefs[l].pcout);
     }

@@ -151,3 +151,38 @@ def test_trained_guess_lowers_the_initial_residual_but_not_the_iterations():
     assert all(r["status"] == [0, 0, 0] for r in ev["rows"])
     assert ev["mean_res0_guess"] < 0.75 * ev["mean_res0_b"], ev
     assert 0.9 < ev["iteration_ratio"] < 1.1, ev
+
+
+@pytest.mark.parametrize("G,B,grad", [(8, 1, True), (8, 3, True), (24, 2, True), (40, 1, True), (72, 1, False)])
+def test_boxes_on_both_sides_of_the_tiled_kernels(G, B, grad):
+    """The tiled kernels take boxes whose side is a multiple of 8 (four rows and steps of eight voxels;
+    the planes of 32 channels up to 56, the weight gradient up to 64), the gathering ones the rest:
+    levels of 8 4 2 1, 24 12 6 3 and 40 20 10 5 voxels, and 72, where only the 16-channel planes still
+    fit.  Bars as above (bfloat16 rounding); a batch gives each of its particles bit for bit."""
+    dda = _dda()
+    p = _params(6)
+    rng = np.random.default_rng(G + B)
+    f = rng.standard_normal((B, G, G, G, 16)) * 0.5
+    f[..., 0] = rng.random((B, G, G, G)) < 0.4
+    f = cn.bf16(f)
+    t = (rng.standard_normal((B, G, G, G, 6)) * 0.3).astype(np.float32)
+    feat = torch.from_numpy(f.astype(np.float32)).cuda().to(torch.bfloat16).reshape(B, G ** 3, 16)
+    with dda.Net(G, p, max_batch=B) as net:
+        out = net.forward(feat)
+        for s in range(B):
+            assert torch.equal(net.forward(feat[s:s + 1].contiguous())[0], out[s])
+        if grad:
+            loss, g = net.grad(feat, torch.from_numpy(t).cuda().reshape(B, G ** 3, 6))
+    ref = cn.forward(p, f[0], bf16_round=True)["out"]
+    o = out[0].cpu().numpy().astype(np.float64).reshape(G, G, G, 6)
+    assert np.linalg.norm(o - ref) < 1e-2 * np.linalg.norm(ref)
+    if not grad:
+        return
+    lo, go = cn.loss_and_grad(p, f, t.astype(np.float64), f[..., 0], bf16_round=True)
+    assert abs(loss - lo) < 1e-2 * lo
+    off = 0
+    for li, (ci, co, *_) in enumerate(cn.LAYERS):
+        for n in (27 * ci * co, co):
+            a, b = g[off:off + n].astype(np.float64), go[off:off + n]
+            assert np.linalg.norm(a - b) <= 3e-2 * np.linalg.norm(b) + 1e-12, (li, n)
+            off += n
