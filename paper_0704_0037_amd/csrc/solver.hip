@@ -41,7 +41,9 @@ struct SolveState {
     double2 eps, delta, beta, eta, cp;
     // Bi-CGSTAB
     double2 rho_b, rho_old, alpha, omega, beta_b;
-    int iter, status, maxit, pending, half, first, stop_after, pad1;  // stop_after: at the limit, end this iteration
+    int iter, status, maxit, pending, half, first;
+    int stop_after;  // at the limit: end this iteration
+    int fresh;       // in the second state: k_stop_after takes it over
 };
 
 // ------------------------------------------------------------------ small helpers
@@ -58,19 +60,22 @@ template <typename R> __device__ __forceinline__ cplx<R> dn(double2 a) { return 
 
 // sum K double2 values over the block (LDS tree, deterministic); result valid in thread 0
 template <int K> __device__ __forceinline__ void block_reduce(double2 (&v)[K], double2 *sh) {
+    static_assert(kVecThreads == 256, "the first wave adds four quarters");
     const int t = threadIdx.x;
     for (int k = 0; k < K; ++k) sh[k * kVecThreads + t] = v[k];
     __syncthreads();
-    for (int h = kVecThreads / 2; h > 0; h >>= 1) {
-        if (t < h)
-            for (int k = 0; k < K; ++k) {
-                double2 a = sh[k * kVecThreads + t], b = sh[k * kVecThreads + t + h];
-                sh[k * kVecThreads + t] = make_double2(a.x + b.x, a.y + b.y);
+    if (t < 64)
+        for (int k = 0; k < K; ++k) {
+            const double2 *q = sh + k * kVecThreads + t;
+            const double2 q0 = q[0], q1 = q[64], q2 = q[128], q3 = q[192];
+            double2 a = make_double2((q0.x + q2.x) + (q1.x + q3.x), (q0.y + q2.y) + (q1.y + q3.y));
+            for (int h = 32; h > 0; h >>= 1) {
+                a.x += __shfl_down(a.x, h);
+                a.y += __shfl_down(a.y, h);
             }
-        __syncthreads();
-    }
-    if (t == 0)
-        for (int k = 0; k < K; ++k) v[k] = sh[k * kVecThreads];
+            if (t == 0) v[k] = sh[k * kVecThreads] = a;
+        }
+    __syncthreads();
 }
 
 // sum partials [nb][K] of one right-hand side into out[K]; every thread of the block gets them
@@ -92,6 +97,56 @@ template <int K> __device__ __forceinline__ void sum_partials(const double2 *p, 
 }
 
 #define VEC_LOOP(n3) for (size_t i = (size_t)blockIdx.x * kVecThreads + threadIdx.x; i < (n3); i += (size_t)gridDim.x * kVecThreads)
+
+// The bilinear-dot partials of the product (k_inv_x) of one right-hand side, summed by the block in
+// the order of a single block of kVecThreads; every thread gets the sum.
+template <typename R> __device__ __forceinline__ double2 sum_dots(const cplx<R> *dots, int ndots, double2 *sh) {
+    double2 v[1] = {make_double2(0, 0)};
+    for (int b = threadIdx.x; b < ndots; b += blockDim.x) {
+        const double2 d = up<R>(dots[b]);
+        v[0].x += d.x;
+        v[0].y += d.y;
+    }
+    block_reduce<1>(v, sh);
+    __syncthreads();
+    const double2 r = sh[0];
+    __syncthreads();
+    return r;
+}
+
+// The scalars between the vector passes of QMR, Bi-CG and Bi-CGSTAB are formed inside the vector kernel
+// that needs them: every block sums the partials itself, in the same order, and block 0 of the
+// right-hand side stores the scalars.  What other blocks of the kernel still read goes to a second
+// state (st2) that the next scalar kernel takes over, and partials go to a second array.  A scalar
+// kernel of its own (one block) cost 5 to 8 us of an iteration: it starts when the last block of the
+// pass before it has ended, and the next pass waits for it.  Per iteration of QMR, Bi-CG and Bi-CGSTAB,
+// with scalar kernels and without: 77, 67, 113 us and 58, 54, 88 (2,176 dipoles), 244, 231, 440 and
+// 229, 217, 416 (195,360 dipoles); from 380,000 dipoles on (1,024 blocks) even.
+// Partials of the product that every block sums (2,352 at 735,904 dipoles, where both ways are even);
+// k_sum_dots sums more of them (24,576 at 256^3).
+constexpr int kBlockDots = 4096;
+template <typename R> __global__ void k_sum_dots(const int *done, const cplx<R> *dots, int ndots, double2 *sum) {
+    __shared__ double2 sh[kVecThreads];
+    const int rhs = blockIdx.x;
+    if (done[rhs]) return;
+    const double2 s = sum_dots<R>(dots + (size_t)rhs * ndots, ndots, sh);
+    if (threadIdx.x == 0) sum[rhs] = s;
+}
+// p^T A p: k_sum_dots' result, or the sum of the partials where that did not run (dsum null)
+template <typename R>
+__device__ __forceinline__ double2 dot_of(const cplx<R> *dots, int ndots, const double2 *dsum, int rhs, double2 *sh) {
+    return dsum ? dsum[rhs] : sum_dots<R>(dots + (size_t)rhs * ndots, ndots, sh);
+}
+
+// Whether a right-hand side is done, where block 0 of the same launch may set the flag meanwhile (every
+// other block then comes to stop by itself too): the waves of one block have to agree.
+__device__ __forceinline__ bool stopped(const int *done) {
+    return __syncthreads_or(*(const volatile int *)done) != 0;
+}
+__device__ __forceinline__ void break_down(SolveState &S, int *done) {
+    S.status = ST_BREAK;
+    *done = 1;
+}
 
 // ============================================================================ QMR
 // r = b - Ax0 (Ax0 given) or b; vt = r; x zeroed when there is no initial guess.
@@ -170,40 +225,25 @@ __global__ void __launch_bounds__(kVecThreads) k_qmr_p0(const SolveState *st, co
     VEC_LOOP(n3) p[off + i] = cscale(vt[off + i], inv);
 }
 
-// eps = p^T A p from the matvec epilogue partials; beta = eps / delta
+// eps = p^T A p; beta = eps / delta; vt = pt - (beta / rho) vt; partials |vt|^2, vt^T vt
 template <typename R>
-__global__ void k_qmr_scal_eps(SolveState *st, int *done, const cplx<R> *dots, int ndots) {
-    __shared__ double2 sh[kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 v[1] = {make_double2(0, 0)};
-    for (int b = threadIdx.x; b < ndots; b += blockDim.x) {
-        const double2 d = up<R>(dots[(size_t)rhs * ndots + b]);
-        v[0].x += d.x;
-        v[0].y += d.y;
-    }
-    block_reduce<1>(v, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
-    S.eps = v[0];
-    if ((S.eps.x == 0 && S.eps.y == 0) || !dfinite(S.eps)) {
-        S.status = ST_BREAK;
-        done[rhs] = 1;
-        return;
-    }
-    S.beta = ddiv(S.eps, S.delta);
-}
-
-// vt = pt - (beta / rho) vt; partials |vt|^2, vt^T vt
-template <typename R>
-__global__ void __launch_bounds__(kVecThreads) k_qmr_vt(const SolveState *st, const int *done, const cplx<R> *pt,
-                                                        cplx<R> *vt, size_t n3, double2 *part) {
+__global__ void __launch_bounds__(kVecThreads) k_qmr_vt(SolveState *st, int *done, const cplx<R> *pt, cplx<R> *vt,
+                                                        size_t n3, double2 *part, const cplx<R> *dots, int ndots,
+                                                        const double2 *dsum) {
     __shared__ double2 sh[2 * kVecThreads];
     const int rhs = blockIdx.y;
-    if (done[rhs]) return;
+    if (stopped(done + rhs)) return;
     const size_t off = (size_t)rhs * n3;
-    const SolveState &S = st[rhs];
-    const cplx<R> c = dn<R>(make_double2(S.beta.x / S.rho, S.beta.y / S.rho));
+    SolveState &S = st[rhs];
+    const double2 eps = dot_of<R>(dots, ndots, dsum, rhs, sh), beta = ddiv(eps, S.delta);
+    const bool ok = !(eps.x == 0 && eps.y == 0) && dfinite(eps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        S.eps = eps;
+        if (ok) S.beta = beta;
+        else break_down(S, done + rhs);
+    }
+    if (!ok) return;
+    const cplx<R> c = dn<R>(make_double2(beta.x / S.rho, beta.y / S.rho));
     double2 acc[2] = {make_double2(0, 0), make_double2(0, 0)};
     VEC_LOOP(n3) {
         const cplx<R> v = csub(pt[off + i], cmul(c, vt[off + i]));
@@ -221,15 +261,8 @@ __global__ void __launch_bounds__(kVecThreads) k_qmr_vt(const SolveState *st, co
     }
 }
 
-// rho_new, theta, gamma, eta and the coefficients of the update pass
-__global__ void k_qmr_scal_2(SolveState *st, int *done, const double2 *part, int nb) {
-    __shared__ double2 sh[2 * kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 s[2];
-    sum_partials<2>(part + (size_t)rhs * nb * 4, nb, s, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
+// rho_new, theta, gamma, eta and the coefficients of the update pass, from |vt|^2 and vt^T vt
+__device__ __forceinline__ void qmr_step(SolveState &S, const double2 (&s)[2]) {
     const double rho_new = sqrt(s[0].x);
     const double bmod = dabs(S.beta);
     const double theta = rho_new / (S.gamma_prev * bmod);
@@ -261,17 +294,26 @@ __global__ void k_qmr_scal_2(SolveState *st, int *done, const double2 *part, int
     S.cp = ddiv(make_double2(rho_new * S.delta.x, rho_new * S.delta.y), S.eps);
 }
 
-// d = eta p + c2 d;  s = eta pt + c2 s;  x += d;  r -= s;  p = vt / rho - cp p;  partial |r|^2
+// d = eta p + c2 d;  s = eta pt + c2 s;  x += d;  r -= s;  p = vt / rho - cp p;  partial |r|^2.
+// The coefficients come from the partials of vt (vpart); the new state goes to st2.
 template <typename R>
 __global__ void __launch_bounds__(kVecThreads) k_qmr_update(const SolveState *st, const int *done, cplx<R> *p,
                                                             const cplx<R> *pt, const cplx<R> *vt, cplx<R> *d,
                                                             cplx<R> *s, cplx<R> *x, cplx<R> *r, size_t n3,
-                                                            double2 *part) {
-    __shared__ double2 sh[kVecThreads];
+                                                            double2 *part, const double2 *vpart, SolveState *st2) {
+    __shared__ double2 sh[2 * kVecThreads];
+    __shared__ SolveState S;
     const int rhs = blockIdx.y;
     if (done[rhs]) return;
     const size_t off = (size_t)rhs * n3;
-    const SolveState &S = st[rhs];
+    double2 q[2];
+    sum_partials<2>(vpart + (size_t)rhs * gridDim.x * 4, gridDim.x, q, sh);
+    if (threadIdx.x == 0) {
+        S = st[rhs];
+        qmr_step(S, q);
+        if (blockIdx.x == 0) st2[rhs] = S;
+    }
+    __syncthreads();
     const cplx<R> eta = dn<R>(S.eta), cp = dn<R>(S.cp);
     const R c2 = (R)S.c2, inv = (R)(S.rho > 0 ? 1.0 / S.rho : 0.0);
     const bool first = S.first;
@@ -296,7 +338,9 @@ __global__ void __launch_bounds__(kVecThreads) k_qmr_update(const SolveState *st
     if (threadIdx.x == 0) part[((size_t)rhs * gridDim.x + blockIdx.x) * 4] = acc[0];
 }
 
-__global__ void k_qmr_scal_3(SolveState *st, int *done, const double2 *part, int nb, double *hist, int hcap) {
+// residual and stopping rule; st2: the state the update formed
+__global__ void k_qmr_scal_3(SolveState *st, int *done, const double2 *part, int nb, double *hist, int hcap,
+                             const SolveState *st2) {
     __shared__ double2 sh[kVecThreads];
     const int rhs = blockIdx.x;
     if (done[rhs]) return;
@@ -304,6 +348,7 @@ __global__ void k_qmr_scal_3(SolveState *st, int *done, const double2 *part, int
     sum_partials<1>(part + (size_t)rhs * nb * 4, nb, s, sh);
     if (threadIdx.x != 0) return;
     SolveState &S = st[rhs];
+    S = st2[rhs];
     S.first = 0;
     S.iter += 1;
     S.res = sqrt(s[0].x) / S.bnorm;
@@ -355,41 +400,26 @@ __global__ void k_bicg_scal_init(SolveState *st, int *done, const double2 *part,
     done[rhs] = 0;
 }
 
-// eps = p^T A p from the matvec epilogue partials; alpha = rho / eps
+// eps = p^T A p; alpha = rho / eps; x += alpha p;  r -= alpha q;  partials |r|^2, r^T r
 template <typename R>
-__global__ void k_bicg_scal_alpha(SolveState *st, int *done, const cplx<R> *dots, int ndots) {
-    __shared__ double2 sh[kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 v[1] = {make_double2(0, 0)};
-    for (int b = threadIdx.x; b < ndots; b += blockDim.x) {
-        const double2 d = up<R>(dots[(size_t)rhs * ndots + b]);
-        v[0].x += d.x;
-        v[0].y += d.y;
-    }
-    block_reduce<1>(v, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
-    S.eps = v[0];
-    if ((S.eps.x == 0 && S.eps.y == 0) || !dfinite(S.eps)) {
-        S.status = ST_BREAK;
-        done[rhs] = 1;
-        return;
-    }
-    S.alpha = ddiv(S.rho_b, S.eps);
-}
-
-// x += alpha p;  r -= alpha q;  partials |r|^2, r^T r
-template <typename R>
-__global__ void __launch_bounds__(kVecThreads) k_bicg_update(const SolveState *st, const int *done,
-                                                             const cplx<R> *__restrict__ p, const cplx<R> *__restrict__ q,
-                                                             cplx<R> *__restrict__ x, cplx<R> *__restrict__ r, size_t n3,
-                                                             double2 *part) {
+__global__ void __launch_bounds__(kVecThreads) k_bicg_update(SolveState *st, int *done, const cplx<R> *__restrict__ p,
+                                                             const cplx<R> *__restrict__ q, cplx<R> *__restrict__ x,
+                                                             cplx<R> *__restrict__ r, size_t n3, double2 *part,
+                                                             const cplx<R> *dots, int ndots, const double2 *dsum) {
     __shared__ double2 sh[2 * kVecThreads];
     const int rhs = blockIdx.y;
-    if (done[rhs]) return;
+    if (stopped(done + rhs)) return;
     const size_t off = (size_t)rhs * n3;
-    const cplx<R> a = dn<R>(st[rhs].alpha);
+    SolveState &S = st[rhs];
+    const double2 eps = dot_of<R>(dots, ndots, dsum, rhs, sh), alpha = ddiv(S.rho_b, eps);
+    const bool ok = !(eps.x == 0 && eps.y == 0) && dfinite(eps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        S.eps = eps;
+        if (ok) S.alpha = alpha;
+        else break_down(S, done + rhs);
+    }
+    if (!ok) return;
+    const cplx<R> a = dn<R>(alpha);
     double2 acc[2] = {make_double2(0, 0), make_double2(0, 0)};
     VEC_LOOP(n3) {
         x[off + i] = cadd(x[off + i], cmul(a, p[off + i]));
@@ -408,38 +438,36 @@ __global__ void __launch_bounds__(kVecThreads) k_bicg_update(const SolveState *s
     }
 }
 
-// residual, stopping rule; beta = rho_new / rho
-__global__ void k_bicg_scal_2(SolveState *st, int *done, const double2 *part, int nb, double *hist, int hcap) {
-    __shared__ double2 sh[2 * kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 s[2];
-    sum_partials<2>(part + (size_t)rhs * nb * 4, nb, s, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
+// residual, stopping rule; beta = rho_new / rho.  Returns whether the right-hand side stops here.
+__device__ __forceinline__ bool bicg_step(SolveState &S, const double2 (&s)[2]) {
     S.iter += 1;
     S.res = sqrt(s[0].x) / S.bnorm;
-    if (hist && hcap > 0) hist[(size_t)rhs * hcap + (S.iter < hcap ? S.iter : hcap - 1)] = S.res;
     if (S.res < S.tol) {
         S.status = ST_CONV;
-        done[rhs] = 1;
-    } else if (!isfinite(S.res) || dabs(s[1]) < kBreakdown * s[0].x || !dfinite(s[1])) {
-        S.status = ST_BREAK;
-        done[rhs] = 1;
-    } else {
-        S.beta_b = ddiv(s[1], S.rho_b);
-        S.rho_b = s[1];
-        // at the limit the iteration still forms p, so that a continued solve starts from a whole
-        // iteration (k_stop_after ends it)
-        if (S.iter >= S.maxit) S.stop_after = 1;
+        return true;
     }
+    if (!isfinite(S.res) || dabs(s[1]) < kBreakdown * s[0].x || !dfinite(s[1])) {
+        S.status = ST_BREAK;
+        return true;
+    }
+    S.beta_b = ddiv(s[1], S.rho_b);
+    S.rho_b = s[1];
+    // at the limit the iteration still forms p, so that a continued solve starts from a whole
+    // iteration (k_stop_after ends it)
+    if (S.iter >= S.maxit) S.stop_after = 1;
+    return false;
 }
-
-// end of an iteration: a right-hand side that reached its limit stops here
-__global__ void k_stop_after(SolveState *st, int *done, int nrhs) {
+// end of an iteration: a right-hand side that reached its limit stops here; st2 (nullable) holds the
+// new state of every right-hand side whose fresh is set
+__global__ void k_stop_after(SolveState *st, int *done, int nrhs, SolveState *st2) {
     const int rhs = blockIdx.x * blockDim.x + threadIdx.x;
-    if (rhs >= nrhs || done[rhs]) return;
+    if (rhs >= nrhs) return;
     SolveState &S = st[rhs];
+    if (st2 && st2[rhs].fresh) {
+        st2[rhs].fresh = 0;
+        S = st2[rhs];
+    }
+    if (done[rhs]) return;
     if (S.stop_after) {
         S.stop_after = 0;
         S.status = ST_MAXIT;
@@ -447,15 +475,33 @@ __global__ void k_stop_after(SolveState *st, int *done, int nrhs) {
     }
 }
 
-// p = r + beta p
+// p = r + beta p.  The step's scalars come from the partials of the update; the new state goes to st2,
+// and a right-hand side that stops keeps its p.
 template <typename R>
-__global__ void __launch_bounds__(kVecThreads) k_bicg_p(const SolveState *st, const int *done,
-                                                        const cplx<R> *__restrict__ r, cplx<R> *__restrict__ p,
-                                                        size_t n3) {
+__global__ void __launch_bounds__(kVecThreads) k_bicg_p(const SolveState *st, int *done, const cplx<R> *__restrict__ r,
+                                                        cplx<R> *__restrict__ p, size_t n3, const double2 *part,
+                                                        SolveState *st2, double *hist, int hcap) {
+    __shared__ double2 sh[2 * kVecThreads];
+    __shared__ SolveState S;
+    __shared__ int stops;
     const int rhs = blockIdx.y;
-    if (done[rhs]) return;
+    if (stopped(done + rhs)) return;
     const size_t off = (size_t)rhs * n3;
-    const cplx<R> b = dn<R>(st[rhs].beta_b);
+    double2 q[2];
+    sum_partials<2>(part + (size_t)rhs * gridDim.x * 4, gridDim.x, q, sh);
+    if (threadIdx.x == 0) {
+        S = st[rhs];
+        stops = bicg_step(S, q);
+        if (blockIdx.x == 0) {
+            S.fresh = 1;
+            st2[rhs] = S;
+            if (hist && hcap > 0) hist[(size_t)rhs * hcap + (S.iter < hcap ? S.iter : hcap - 1)] = S.res;
+            if (stops) done[rhs] = 1;
+        }
+    }
+    __syncthreads();
+    if (stops) return;
+    const cplx<R> b = dn<R>(S.beta_b);
     VEC_LOOP(n3) p[off + i] = cadd(r[off + i], cmul(b, p[off + i]));
 }
 
@@ -705,32 +751,25 @@ __global__ void __launch_bounds__(kVecThreads) k_bi_dots(const int *done, const 
     }
 }
 
-// alpha = rho / (rs^H v)
-__global__ void k_bi_scal_alpha(SolveState *st, int *done, const double2 *part, int nb) {
-    __shared__ double2 sh[2 * kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 s[2];
-    sum_partials<2>(part + (size_t)rhs * nb * 4, nb, s, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
-    if ((s[0].x == 0 && s[0].y == 0) || !dfinite(s[0])) {
-        S.status = ST_BREAK;
-        done[rhs] = 1;
-        return;
-    }
-    S.alpha = ddiv(S.rho_b, s[0]);
-}
-
-// s = r - alpha v; partial |s|^2
+// alpha = rho / (rs^H v); s = r - alpha v; partial |s|^2
 template <typename R>
-__global__ void __launch_bounds__(kVecThreads) k_bi_s(const SolveState *st, const int *done, const cplx<R> *r,
-                                                      const cplx<R> *v, cplx<R> *s, size_t n3, double2 *part) {
-    __shared__ double2 sh[kVecThreads];
+__global__ void __launch_bounds__(kVecThreads) k_bi_s(SolveState *st, int *done, const cplx<R> *r, const cplx<R> *v,
+                                                      cplx<R> *s, size_t n3, double2 *part, const double2 *vpart) {
+    __shared__ double2 sh[2 * kVecThreads];
     const int rhs = blockIdx.y;
-    if (done[rhs]) return;
+    if (stopped(done + rhs)) return;
     const size_t off = (size_t)rhs * n3;
-    const cplx<R> a = dn<R>(st[rhs].alpha);
+    SolveState &S = st[rhs];
+    double2 q[2];
+    sum_partials<2>(vpart + (size_t)rhs * gridDim.x * 4, gridDim.x, q, sh);
+    const bool ok = !(q[0].x == 0 && q[0].y == 0) && dfinite(q[0]);
+    const double2 alpha = ddiv(S.rho_b, q[0]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (ok) S.alpha = alpha;
+        else break_down(S, done + rhs);
+    }
+    if (!ok) return;
+    const cplx<R> a = dn<R>(alpha);
     double2 acc[1] = {make_double2(0, 0)};
     VEC_LOOP(n3) {
         const cplx<R> si = csub(r[off + i], cmul(a, v[off + i]));
@@ -742,50 +781,40 @@ __global__ void __launch_bounds__(kVecThreads) k_bi_s(const SolveState *st, cons
     if (threadIdx.x == 0) part[((size_t)rhs * gridDim.x + blockIdx.x) * 4] = acc[0];
 }
 
-__global__ void k_bi_scal_s(SolveState *st, const int *done, const double2 *part, int nb) {
-    __shared__ double2 sh[kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 s[1];
-    sum_partials<1>(part + (size_t)rhs * nb * 4, nb, s, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
-    S.snorm = sqrt(s[0].x);
-    S.half = (S.snorm / S.bnorm < S.tol) ? 1 : 0;
-}
-
-// omega = (t^H s) / (t^H t), or 0 when s already met the tolerance
-__global__ void k_bi_scal_omega(SolveState *st, int *done, const double2 *part, int nb) {
-    __shared__ double2 sh[2 * kVecThreads];
-    const int rhs = blockIdx.x;
-    if (done[rhs]) return;
-    double2 s[2];
-    sum_partials<2>(part + (size_t)rhs * nb * 4, nb, s, sh);
-    if (threadIdx.x != 0) return;
-    SolveState &S = st[rhs];
-    if (S.half) {
-        S.omega = make_double2(0, 0);
-        return;
+// omega = (t^H s) / (t^H t), or 0 when s already met the tolerance; false at a breakdown
+__device__ __forceinline__ bool bi_omega(bool half, const double2 (&s)[2], double2 &omega) {
+    if (half) {
+        omega = make_double2(0, 0);
+        return true;
     }
-    if (s[1].x == 0 || !isfinite(s[1].x)) {
-        S.status = ST_BREAK;
-        done[rhs] = 1;
-        return;
-    }
-    S.omega = make_double2(s[0].x / s[1].x, s[0].y / s[1].x);
+    if (s[1].x == 0 || !isfinite(s[1].x)) return false;
+    omega = make_double2(s[0].x / s[1].x, s[0].y / s[1].x);
+    return true;
 }
-
-// x += alpha p + omega s;  r = s - omega t;  partials |r|^2, rs^H r
+// x += alpha p + omega s;  r = s - omega t;  partials |r|^2, rs^H r (entries 1 and 2 of part).
+// |s|^2 comes from entry 0 of part, omega from the partials of t^H s and t^H t (tpart).
 template <typename R>
-__global__ void __launch_bounds__(kVecThreads) k_bi_x(const SolveState *st, const int *done, const cplx<R> *p,
-                                                      const cplx<R> *s, const cplx<R> *t, const cplx<R> *rs,
-                                                      cplx<R> *x, cplx<R> *r, size_t n3, double2 *part) {
+__global__ void __launch_bounds__(kVecThreads) k_bi_x(SolveState *st, int *done, const cplx<R> *p, const cplx<R> *s,
+                                                      const cplx<R> *t, const cplx<R> *rs, cplx<R> *x, cplx<R> *r,
+                                                      size_t n3, double2 *part, const double2 *tpart) {
     __shared__ double2 sh[2 * kVecThreads];
     const int rhs = blockIdx.y;
-    if (done[rhs]) return;
+    if (stopped(done + rhs)) return;
     const size_t off = (size_t)rhs * n3;
-    const SolveState &S = st[rhs];
-    const cplx<R> a = dn<R>(S.alpha), om = dn<R>(S.omega);
+    SolveState &S = st[rhs];
+    double2 n[1], q[2], omega;
+    sum_partials<1>(part + (size_t)rhs * gridDim.x * 4, gridDim.x, n, sh);
+    sum_partials<2>(tpart + (size_t)rhs * gridDim.x * 4, gridDim.x, q, sh);
+    const double snorm = sqrt(n[0].x);
+    const bool half = snorm / S.bnorm < S.tol, ok = bi_omega(half, q, omega);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        S.snorm = snorm;
+        S.half = half ? 1 : 0;
+        if (ok) S.omega = omega;
+        else break_down(S, done + rhs);
+    }
+    if (!ok) return;
+    const cplx<R> a = dn<R>(S.alpha), om = dn<R>(omega);
     double2 acc[2] = {make_double2(0, 0), make_double2(0, 0)};
     VEC_LOOP(n3) {
         const cplx<R> si = s[off + i];
@@ -800,8 +829,8 @@ __global__ void __launch_bounds__(kVecThreads) k_bi_x(const SolveState *st, cons
     block_reduce<2>(acc, sh);
     if (threadIdx.x == 0) {
         double2 *pp = part + ((size_t)rhs * gridDim.x + blockIdx.x) * 4;
-        pp[0] = acc[0];
-        pp[1] = acc[1];
+        pp[1] = acc[0];
+        pp[2] = acc[1];
     }
 }
 
@@ -889,6 +918,8 @@ struct Bufs {
     SolveState *st = nullptr;
     int *done = nullptr;
     double2 *part = nullptr;
+    double2 *part2 = nullptr;    // partials of kernels that still read part
+    SolveState *st2 = nullptr;   // states formed by kernels that still read st
     double *hist = nullptr;
     int hcap = 0;
     double2 *scratch = nullptr;  // 4 nrhs + 16 entries of small device scratch
@@ -961,8 +992,8 @@ static dda_status ensure_bufs(Ctx &c, Bufs &B, int nrhs, int hcap) {
     B.nb = (int)std::min<size_t>(1024, (B.n3 + kVecThreads * 4 - 1) / (kVecThreads * 4));
     if (B.nb < 1) B.nb = 1;
     B.hcap = hcap;
-    const size_t bytes = nrhs * sizeof(SolveState) + 256 + nrhs * sizeof(int) * 2 + 256 +
-                         (size_t)nrhs * B.nb * 4 * sizeof(double2) + 256 + (size_t)nrhs * hcap * sizeof(double) + 256 +
+    const size_t bytes = 2 * (nrhs * sizeof(SolveState) + 256) + nrhs * sizeof(int) * 2 + 256 +
+                         2 * ((size_t)nrhs * B.nb * 4 * sizeof(double2) + 256) + (size_t)nrhs * hcap * sizeof(double) + 256 +
                          (4 * (size_t)nrhs + 16) * sizeof(double2) + 256;
     if (c.sbuf_bytes < bytes) {
         DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
@@ -984,6 +1015,8 @@ static dda_status ensure_bufs(Ctx &c, Bufs &B, int nrhs, int hcap) {
     B.part = (double2 *)take((size_t)nrhs * B.nb * 4 * sizeof(double2));
     B.hist = hcap > 0 ? (double *)take((size_t)nrhs * hcap * sizeof(double)) : nullptr;
     B.scratch = (double2 *)take((4 * (size_t)nrhs + 16) * sizeof(double2));
+    B.part2 = (double2 *)take((size_t)nrhs * B.nb * 4 * sizeof(double2));
+    B.st2 = (SolveState *)take(nrhs * sizeof(SolveState));
     const size_t hb = 64 + nrhs * (sizeof(SolveState) + 2 * sizeof(int) + 4 * sizeof(double2));
     if (c.hbuf_bytes < hb) {
         if (c.hbuf) (void)hipHostFree(c.hbuf);
@@ -1006,6 +1039,7 @@ static dda_status init_states(Ctx &c, Bufs &B, double tol, int maxit, const int 
         s.maxit = maxit;
     }
     DDA_HIP_CHECK(hipMemcpyAsync(B.st, h.data(), h.size() * sizeof(SolveState), hipMemcpyHostToDevice, c.stream));
+    DDA_HIP_CHECK(hipMemcpyAsync(B.st2, h.data(), h.size() * sizeof(SolveState), hipMemcpyHostToDevice, c.stream));
     std::vector<int> d(B.nrhs, 0);
     if (active)
         for (int r = 0; r < B.nrhs; ++r) d[r] = active[r] ? 0 : 1;
@@ -1141,6 +1175,10 @@ template <typename R> static dda_status enqueue_iterations(Run<R> &k, int count)
     const int ndots = (int)(k.mixed ? dots_per_rhs<float>(c) : dots_per_rhs<R>(c));
     cplx<R> *x = k.x;
     dda_status st;
+    const double2 *dsum = ndots > kBlockDots ? B.part2 : nullptr;
+    auto sum_dots_first = [&] {
+        if (dsum) hipLaunchKernelGGL(k_sum_dots<R>, dim3(nrhs), vb, 0, s, B.done, w.dots, ndots, B.part2);
+    };
     for (int it = 0; it < count; ++it) {
         if (k.solver == DDA_CGNR) {
             if ((st = run_matvec(k, v.p, v.pt, nullptr, B.done)) != DDA_OK) return st;  // w = A p
@@ -1152,34 +1190,31 @@ template <typename R> static dda_status enqueue_iterations(Run<R> &k, int count)
             hipLaunchKernelGGL(k_cgnr_norm<R>, vg, vb, 0, s, B.done, v.d, n3, B.part);
             hipLaunchKernelGGL(k_cgnr_scal, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb, 2);
             hipLaunchKernelGGL(k_cgnr_p<R>, vg, vb, 0, s, B.st, B.done, v.d, v.p, n3, 0);
-            hipLaunchKernelGGL(k_stop_after, dim3((nrhs + 63) / 64), dim3(64), 0, s, B.st, B.done, nrhs);
+            hipLaunchKernelGGL(k_stop_after, dim3((nrhs + 63) / 64), dim3(64), 0, s, B.st, B.done, nrhs,
+                               (SolveState *)nullptr);
         } else if (k.solver == DDA_BICG) {
             if ((st = run_matvec(k, v.p, v.pt, w.dots, B.done)) != DDA_OK) return st;
-            hipLaunchKernelGGL(k_bicg_scal_alpha<R>, dim3(nrhs), vb, 0, s, B.st, B.done, w.dots, ndots);
-            hipLaunchKernelGGL(k_bicg_update<R>, vg, vb, 0, s, B.st, B.done, v.p, v.pt, x, v.r, n3, B.part);
-            hipLaunchKernelGGL(k_bicg_scal_2, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb, B.hist, B.hcap);
-            hipLaunchKernelGGL(k_bicg_p<R>, vg, vb, 0, s, B.st, B.done, v.r, v.p, n3);
-            hipLaunchKernelGGL(k_stop_after, dim3((nrhs + 63) / 64), dim3(64), 0, s, B.st, B.done, nrhs);
+            sum_dots_first();
+            hipLaunchKernelGGL(k_bicg_update<R>, vg, vb, 0, s, B.st, B.done, v.p, v.pt, x, v.r, n3, B.part, w.dots,
+                               ndots, dsum);
+            hipLaunchKernelGGL(k_bicg_p<R>, vg, vb, 0, s, B.st, B.done, v.r, v.p, n3, B.part, B.st2, B.hist, B.hcap);
+            hipLaunchKernelGGL(k_stop_after, dim3((nrhs + 63) / 64), dim3(64), 0, s, B.st, B.done, nrhs, B.st2);
         } else if (k.solver == DDA_QMR) {
             if ((st = run_matvec(k, v.p, v.pt, w.dots, B.done)) != DDA_OK) return st;
-            hipLaunchKernelGGL(k_qmr_scal_eps<R>, dim3(nrhs), vb, 0, s, B.st, B.done, w.dots, ndots);
-            hipLaunchKernelGGL(k_qmr_vt<R>, vg, vb, 0, s, B.st, B.done, v.pt, v.vt, n3, B.part);
-            hipLaunchKernelGGL(k_qmr_scal_2, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb);
+            sum_dots_first();
+            hipLaunchKernelGGL(k_qmr_vt<R>, vg, vb, 0, s, B.st, B.done, v.pt, v.vt, n3, B.part, w.dots, ndots, dsum);
             hipLaunchKernelGGL(k_qmr_update<R>, vg, vb, 0, s, B.st, B.done, v.p, v.pt, v.vt, v.d, v.s, x, v.r, n3,
-                               B.part);
-            hipLaunchKernelGGL(k_qmr_scal_3, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb, B.hist, B.hcap);
+                               B.part2, B.part, B.st2);
+            hipLaunchKernelGGL(k_qmr_scal_3, dim3(nrhs), vb, 0, s, B.st, B.done, B.part2, B.nb, B.hist, B.hcap, B.st2);
         } else {
             hipLaunchKernelGGL(k_bi_p<R>, vg, vb, 0, s, B.st, B.done, v.r, v.p, v.v, n3);
             if ((st = run_matvec(k, v.p, v.v, nullptr, B.done)) != DDA_OK) return st;
             hipLaunchKernelGGL(k_bi_dots<R>, vg, vb, 0, s, B.done, v.rs, v.v, n3, B.part, 0);
-            hipLaunchKernelGGL(k_bi_scal_alpha, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb);
-            hipLaunchKernelGGL(k_bi_s<R>, vg, vb, 0, s, B.st, B.done, v.r, v.v, v.s, n3, B.part);
-            hipLaunchKernelGGL(k_bi_scal_s, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb);
+            hipLaunchKernelGGL(k_bi_s<R>, vg, vb, 0, s, B.st, B.done, v.r, v.v, v.s, n3, B.part2, B.part);
             if ((st = run_matvec(k, v.s, v.t, nullptr, B.done)) != DDA_OK) return st;
             hipLaunchKernelGGL(k_bi_dots<R>, vg, vb, 0, s, B.done, v.t, v.s, n3, B.part, 1);
-            hipLaunchKernelGGL(k_bi_scal_omega, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb);
-            hipLaunchKernelGGL(k_bi_x<R>, vg, vb, 0, s, B.st, B.done, v.p, v.s, v.t, v.rs, x, v.r, n3, B.part);
-            hipLaunchKernelGGL(k_bi_scal_end, dim3(nrhs), vb, 0, s, B.st, B.done, B.part, B.nb, B.hist, B.hcap);
+            hipLaunchKernelGGL(k_bi_x<R>, vg, vb, 0, s, B.st, B.done, v.p, v.s, v.t, v.rs, x, v.r, n3, B.part2, B.part);
+            hipLaunchKernelGGL(k_bi_scal_end, dim3(nrhs), vb, 0, s, B.st, B.done, B.part2 + 1, B.nb, B.hist, B.hcap);
         }
     }
     DDA_HIP_CHECK(hipGetLastError());
@@ -1584,6 +1619,7 @@ static dda_status prepare_resume(Ctx &c, Run<double> &k, const dda_beam *beams, 
     std::vector<int> d(nrhs);
     for (int r = 0; r < nrhs; ++r) {
         d[r] = 1;
+        h[r].fresh = 0;
         if (h[r].status == ST_MAXIT) {
             h[r].status = ST_RUN;
             h[r].maxit = h[r].iter + o.maxit;
@@ -1592,6 +1628,7 @@ static dda_status prepare_resume(Ctx &c, Run<double> &k, const dda_beam *beams, 
         }
     }
     DDA_HIP_CHECK(hipMemcpyAsync(k.B.st, h.data(), nrhs * sizeof(SolveState), hipMemcpyHostToDevice, c.stream));
+    DDA_HIP_CHECK(hipMemcpyAsync(k.B.st2, h.data(), nrhs * sizeof(SolveState), hipMemcpyHostToDevice, c.stream));
     DDA_HIP_CHECK(hipMemcpyAsync(k.B.done, d.data(), nrhs * sizeof(int), hipMemcpyHostToDevice, c.stream));
     DDA_HIP_CHECK(hipStreamSynchronize(c.stream));
     return run_resume(k);

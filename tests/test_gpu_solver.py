@@ -880,3 +880,34 @@ def test_farfield_in_rings_about_an_axis(axis, rings):
         scale = np.abs(ref).max()
         assert np.abs(F - ref).max() < 1e-12 * scale
         assert np.abs(G.reshape(per, nrun, 3).transpose(1, 0, 2) - ref).max() < 1e-12 * scale
+
+
+@pytest.mark.parametrize("solver", ["QMR", "BICG", "BICGSTAB"])
+@pytest.mark.parametrize("n", [1, 341, 342, 87381, 87382, (40, 40, 2)])
+def test_scalars_formed_in_the_vector_kernels(solver, n):
+    """Particles on both sides of one block and of 256 blocks of partial sums (one per thread of the
+    block that adds them): the history falls to the tolerance, the residual of the
+    returned vector is the last one of the history (recursive and true residuals part by rounding and the
+    iterations' growth of it, far below the tolerance of 1e-7), and a second right-hand side that is
+    done before the first iteration keeps its vector.  The flat box, at one row a block, has
+    more partial sums of the product (4,800) than every block adds by itself."""
+    dda = _dda()
+    if isinstance(n, tuple):
+        mask = np.ones(n, np.uint8)
+    else:
+        side = 8 if n < 400 else 48
+        mask = np.zeros(side ** 3, np.uint8)
+        mask[:n] = 1
+        mask = mask.reshape(side, side, side)
+    with dda.Context(mask, 1.2 + 0.02j, 0.2, lines_per_block=1 if isinstance(n, tuple) else 0) as ctx:
+        beams = [inputs.X_POL, inputs.Y_POL]
+        first, _, st = ctx.solve([beams[1]], tol=1e-12, solver=getattr(dda, solver))
+        assert st == 0
+        x0 = torch.stack([torch.zeros_like(first[0]), first[0]])
+        x, info, st = ctx.solve(beams, tol=1e-7, solver=getattr(dda, solver), x0=x0, history=500)
+        assert st == 0 and info[1]["iters"] == 0 and torch.equal(x[1], first[0])
+        b = ctx.rhs(beams[0])
+        r = (b - ctx.matvec(beams[0], x[0])).norm() / b.norm()
+        h = info[0]["res_hist"]
+        assert len(h) == info[0]["iters"] + 1 and h[-1] < 1e-7 <= min(h[:-1])
+        assert abs(r.item() - h[-1]) < 1e-9
