@@ -45,7 +45,7 @@ struct Ctx {
     std::vector<int32_t> lin_host;  // linear cell index of each dipole
 
     int *gmap = nullptr;            // device [nz][ny][nx] -> dipole index or -1
-    int2 *rows = nullptr;           // device [nz][ny] single-run descriptors of the rows (x passes)
+    int2 *rows = nullptr;           // device [nz][ny] single-run descriptors of the rows, then [nz] y ranges of the planes
     // a batch of particles on one grid (pack_setup): gmap and rows hold one map per right-hand side,
     // these many elements apart (0 for a single particle); the tensor, twiddles and plans are
     // borrowed from the member whose grid is the batch's

@@ -32,7 +32,7 @@ constexpr int kMaxRadixZ = 8;   // the fused z pass keeps three components in re
 // precision transform)
 // rows: per (y, z) row of the grid, {x0 | x1 << 16, first dipole} when the row's non-void cells are
 // the single run x0 <= x < x1 (dipole indices then follow from x without a lookup), x0 = 0xFFFF
-// when they are not (the cell map gmap is used)
+// when they are not (the cell map gmap is used).  The y ranges of the planes follow the rows.
 __device__ __forceinline__ bool row_run(const int2 *__restrict__ rows, int row, int &x0, int &x1, int &id0) {
     const int2 rr = rows[row];
     x0 = rr.x & 0xFFFF;
@@ -40,6 +40,16 @@ __device__ __forceinline__ bool row_run(const int2 *__restrict__ rows, int row, 
     id0 = rr.y;
     return x0 != 0xFFFF;
 }
+
+// y range of a plane z that holds dipoles: entry z after the rows (ext), y0 | y1 << 16.  Lines outside
+// it are zero before the x pass and unused after it; EXT: they are left out.
+template <bool EXT> __device__ __forceinline__ int plane_range(const int2 *__restrict__ ext, size_t stride, int z, int ny) {
+    if constexpr (EXT) return ext[stride + z].x;
+    else return ny << 16;
+}
+__device__ __forceinline__ bool in_range(int e, int y) { return y >= (e & 0xFFFF) && y < (e >> 16); }
+// whether NL lines from y0 are all outside the range
+__device__ __forceinline__ bool off_range(int e, int y0, int NL) { return y0 + NL <= (e & 0xFFFF) || y0 >= (e >> 16); }
 
 // Workgroups go to the eight XCDs round-robin by index.  The x and y passes renumber them so that
 // each XCD runs one contiguous range of the logical block order: the neighbouring tiles that read
@@ -56,9 +66,9 @@ __device__ __forceinline__ int xcd_block() {
 #endif
 }
 
-template <typename R, int LC, typename RX = R>
+template <typename R, int LC, typename RX, bool EXT>
 __global__ void __launch_bounds__(max_threads<R>()) k_fwd_x(const int *__restrict__ gmap, const int2 *__restrict__ rows,
-                                                size_t gstride, size_t rstride, const cplx<RX> *__restrict__ x,
+                                                const int2 *__restrict__ ext, size_t gstride, size_t rstride, const cplx<RX> *__restrict__ x,
                                                 cplx<R> *__restrict__ B1, int nx, int ny, int nz, int N,
                                                 FftPlan pl_rt, const cplx<R> *__restrict__ twall, int lnl,
                                                 const int *__restrict__ done) {
@@ -80,6 +90,8 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_x(const int *__restric
     // a batch of particles (right-hand sides with their own dipoles on a common grid): this one's maps
     gmap += (size_t)(c / 3) * gstride;
     rows += (size_t)(c / 3) * rstride;
+    const int e = plane_range<EXT>(ext, (size_t)(c / 3) * rstride, z, ny);
+    if (EXT && off_range(e, y0, NL)) return;
     const int t = threadIdx.x;
     const cplx<RX> *xc = x + (size_t)c * N;
     {   // pass 0 from global, lines along lanes' j (x contiguous)
@@ -114,17 +126,18 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_x(const int *__restric
     C *dstc = B1 + ((size_t)c * nz + z) * (size_t)L * nyp;
     if (NP >= 2) {  // last pass to global, lanes over lines (y contiguous in B1)
         const int line = t & (NL - 1), j = t >> lnl, y = y0 + line;
+        const bool yw = in_range(e, y);
         const int Rp = RL, Ns = NSL;
         for (int jb = j; jb < L / Rp; jb += TPL) {
             C a[kMaxRadix];
             const C *ln = lds + line * S;
             load_rt<-1, kMaxRadix>(a, Rp, jb, L, Ns, tw, [&](int i) { return ln[pidx(i)]; });
-            if (y < ny) store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) { st_stream(&dstc[(size_t)i * nyp + y], v); });
+            if (yw) store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) { st_stream(&dstc[(size_t)i * nyp + y], v); });
         }
     } else {
-        for (int e = t; e < NL * L; e += blockDim.x) {
-            const int line = e & (NL - 1), i = e >> lnl, y = y0 + line;
-            if (y < ny) dstc[(size_t)i * nyp + y] = lds[line * S + pidx(i)];
+        for (int q = t; q < NL * L; q += blockDim.x) {
+            const int line = q & (NL - 1), i = q >> lnl, y = y0 + line;
+            if (in_range(e, y)) dstc[(size_t)i * nyp + y] = lds[line * S + pidx(i)];
         }
     }
 }
@@ -132,8 +145,9 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_x(const int *__restric
 // ---------------------------------------------------------------- K2: forward y pass
 // Block: component c, column kx, NL consecutive planes z.  Reads B1 lines along y (n_y
 // nonzero entries), transforms, writes B2[ky][kx][c][z].
-template <typename R, int LC>
-__global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const cplx<R> *__restrict__ B1, cplx<R> *__restrict__ B2, int ny,
+template <typename R, int LC, bool EXT>
+__global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const int2 *__restrict__ ext, size_t rstride,
+                                                const cplx<R> *__restrict__ B1, cplx<R> *__restrict__ B2, int ny,
                                                 int nz, int Lx, int ncomp, FftPlan pl_rt,
                                                 const cplx<R> *__restrict__ twall, int lnl,
                                                 const int *__restrict__ done) {
@@ -156,11 +170,21 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const cplx<R> *__res
     {
         const int line = t / TPL, j = t % TPL, z = z0 + line;
         const bool zok = z < nz;
+        const int e = zok ? plane_range<EXT>(ext, (size_t)(c / 3) * rstride, z, ny) : 0;
         const C *src = B1 + (((size_t)c * nz + (zok ? z : 0)) * Lx + kx) * row_pitch(ny);
         for (int jb = j; jb < L / R0; jb += TPL) {
             C a[kMaxRadix];
-            load_rt<-1, kMaxRadix, true>(a, R0, jb, L, 1, tw,
-                                   [&](int i) -> C { return (zok && i < ny) ? ld_stream(&src[i]) : czero<C>(); });
+            // a line's loads wait for its range; where the waves hold pieces of several planes' lines
+            // (L = 192, 320) they don't: what lies outside is read and dropped (320, two vectors: 455,
+            // against 470 us)
+            if constexpr (!EXT || wave_lines<LC, kMaxRadix>())
+                load_rt<-1, kMaxRadix, true>(a, R0, jb, L, 1, tw,
+                                   [&](int i) -> C { return in_range(e, i) ? ld_stream(&src[i]) : czero<C>(); });
+            else
+                load_rt<-1, kMaxRadix, true>(a, R0, jb, L, 1, tw, [&](int i) -> C {
+                    const C v = (zok && i < ny) ? ld_stream(&src[i]) : czero<C>();
+                    return in_range(e, i) ? v : czero<C>();
+                });
             C *ln = lds + line * S;
             store_rt<kMaxRadix>(a, R0, jb, 1, [&](int i, C v) { ln[pidx(i)] = v; });
         }
@@ -392,8 +416,9 @@ __host__ __device__ constexpr size_t zmul_lds_elems(int Lz) {
 // ---------------------------------------------------------------- K4: inverse y pass
 // Block: component c, column kx, NL consecutive planes z.  Reads B2 along ky (all Ly entries),
 // inverse transform, keeps y < ny, writes B1[c][z][kx][y].
-template <typename R, int LC>
-__global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const cplx<R> *__restrict__ B2, cplx<R> *__restrict__ B1, int ny,
+template <typename R, int LC, bool EXT>
+__global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const int2 *__restrict__ ext, size_t rstride,
+                                                const cplx<R> *__restrict__ B2, cplx<R> *__restrict__ B1, int ny,
                                                 int nz, int Lx, int ncomp, FftPlan pl_rt,
                                                 const cplx<R> *__restrict__ twall, int lnl,
                                                 const int *__restrict__ done) {
@@ -413,6 +438,8 @@ __global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const cplx<R> *__res
     const int c = b / Lx;
     if (done && done[c / 3]) return;
     const int t = threadIdx.x;
+    const int line = t / TPL, j = t % TPL, z = z0 + line;
+    const int e = z < nz ? plane_range<EXT>(ext, (size_t)(c / 3) * rstride, z, ny) : 0;
     const int nzp = row_pitch(nz);
 #if DDA_B2_COLMAJOR
     const size_t kystride = (size_t)nzp;
@@ -434,7 +461,6 @@ __global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const cplx<R> *__res
     }
     __syncthreads();
     lds_passes<+1, kMaxRadix, LC, true>(lds + (t / TPL) * S, pl_rt, 1, NP - 1, t % TPL, tw);
-    const int line = t / TPL, j = t % TPL, z = z0 + line;
     C *dst = B1 + (((size_t)c * nz + (z < nz ? z : 0)) * Lx + kx) * row_pitch(ny);
     if (NP >= 2) {
         const int Rp = RL, Ns = NSL;
@@ -442,12 +468,12 @@ __global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const cplx<R> *__res
             C a[kMaxRadix];
             const C *ln = lds + line * S;
             load_rt<+1, kMaxRadix>(a, Rp, jb, L, Ns, tw, [&](int i) { return ln[pidx(i)]; });
-            if (z < nz) store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) {
-                if (i < ny) st_stream(&dst[i], v);
+            store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) {
+                if (in_range(e, i)) st_stream(&dst[i], v);
             });
         }
-    } else if (z < nz) {
-        for (int i = j; i < ny; i += TPL) dst[i] = lds[line * S + pidx(i)];
+    } else {
+        for (int i = (e & 0xFFFF) + j; i < (e >> 16); i += TPL) dst[i] = lds[line * S + pidx(i)];
     }
 }
 
@@ -475,9 +501,9 @@ __device__ __forceinline__ cplx<R> block_sum(cplx<R> v, cplx<R> *scratch) {
 
 // RX: precision of x, y, the scale and the dots (the transform runs in R; with R = float and
 // RX = double the epilogue y = x - s v and the dot sums are formed in double)
-template <typename R, int LC, typename RX = R>
+template <typename R, int LC, typename RX, bool EXT>
 __global__ void __launch_bounds__(max_threads<R>()) k_inv_x(const int *__restrict__ gmap, const int2 *__restrict__ rows,
-                                                size_t gstride, size_t rstride, const cplx<R> *__restrict__ B1,
+                                                const int2 *__restrict__ ext, size_t gstride, size_t rstride, const cplx<R> *__restrict__ B1,
                                                 const cplx<RX> *__restrict__ xin, cplx<RX> *__restrict__ yout,
                                                 int nx, int ny, int nz, int N, FftPlan pl_rt,
                                                 const cplx<R> *__restrict__ twall, int lnl,
@@ -503,11 +529,16 @@ __global__ void __launch_bounds__(max_threads<R>()) k_inv_x(const int *__restric
     gmap += (size_t)(c / 3) * gstride;
     rows += (size_t)(c / 3) * rstride;
     const int t = threadIdx.x;
+    const int e = plane_range<EXT>(ext, (size_t)(c / 3) * rstride, z, ny);
+    if (EXT && off_range(e, y0, NL)) {
+        if (dots && t == 0) dots[blk] = czero<CX>();
+        return;
+    }
     const int nyp = row_pitch(ny);
     const C *src = B1 + ((size_t)c * nz + z) * (size_t)L * nyp;
     {   // pass 0 from global, lanes over lines (y contiguous in B1)
         const int line = t & (NL - 1), j = t >> lnl, y = y0 + line;
-        const bool yok = y < ny;
+        const bool yok = in_range(e, y);
         for (int jb = j; jb < L / R0; jb += TPL) {
             C a[kMaxRadix];
             load_rt<+1, kMaxRadix>(a, R0, jb, L, 1, tw,

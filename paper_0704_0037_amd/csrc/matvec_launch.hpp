@@ -37,28 +37,17 @@ template <class K> inline void allow_lds(K kernel, size_t bytes) {
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-#define DDA_DISPATCH(LEN, KERNEL, BYTES, ...)                                          \
-    switch (LEN) {                                                                     \
-        DDA_SPECIALIZED_LENGTHS(DDA_CASE_##KERNEL)                                     \
-        default:                                                                       \
-            allow_lds(&KERNEL<R, 0>, BYTES);                                           \
-            hipLaunchKernelGGL((KERNEL<R, 0>), __VA_ARGS__);                           \
-            break;                                                                     \
+// LAUNCH(L) for a length with specialized kernels, LAUNCH(0) (planned at run time) for the others
+#define DDA_DISPATCH(LEN, LAUNCH)                     \
+    switch (LEN) {                                    \
+        DDA_SPECIALIZED_LENGTHS(DDA_CASE_##LAUNCH)    \
+        default: LAUNCH(0) break;                     \
     }
-// the x passes also carry the precision of the vectors
-#define DDA_DISPATCH_X(LEN, KERNEL, BYTES, ...)                                        \
-    switch (LEN) {                                                                     \
-        DDA_SPECIALIZED_LENGTHS(DDA_CASE_##KERNEL)                                     \
-        default:                                                                       \
-            allow_lds(&KERNEL<R, 0, RX>, BYTES);                                       \
-            hipLaunchKernelGGL((KERNEL<R, 0, RX>), __VA_ARGS__);                       \
-            break;                                                                     \
-    }
-#define DDA_CASE_k_fwd_x(L) case L: allow_lds(&k_fwd_x<R, L, RX>, DDA_BYTES); hipLaunchKernelGGL((k_fwd_x<R, L, RX>), DDA_ARGS); break;
-#define DDA_CASE_k_fwd_y(L) case L: allow_lds(&k_fwd_y<R, L>, DDA_BYTES); hipLaunchKernelGGL((k_fwd_y<R, L>), DDA_ARGS); break;
+#define DDA_CASE_fwd_x(L) case L: fwd_x(L) break;
+#define DDA_CASE_fwd_y(L) case L: fwd_y(L) break;
+#define DDA_CASE_inv_y(L) case L: inv_y(L) break;
+#define DDA_CASE_inv_x(L) case L: inv_x(L) break;
 #define DDA_CASE_zcol(L) case L: zcol_launch<R, L>(c, w.B2, gh, nrhs, tw, s, done); break;
-#define DDA_CASE_k_inv_y(L) case L: allow_lds(&k_inv_y<R, L>, DDA_BYTES); hipLaunchKernelGGL((k_inv_y<R, L>), DDA_ARGS); break;
-#define DDA_CASE_k_inv_x(L) case L: allow_lds(&k_inv_x<R, L, RX>, DDA_BYTES); hipLaunchKernelGGL((k_inv_x<R, L, RX>), DDA_ARGS); break;
 
 // Block shape of the column kernel: up to four waves over opb octant columns, which take
 // ceil(4 nrhs opb / (W CPW)) rounds.  The smallest opb whose estimate is not beaten by 10 %: turns of
@@ -105,13 +94,12 @@ inline void zcol_launch(const Ctx &c, cplx<R> *B2, const cplx<R> *gh, int nrhs, 
 }
 
 // Transforms in precision R on the work buffers of precision R (the context's, or the
-// intermediates B1 / B2 of `wk` when given); x, y, scale and dots in RX.
-template <typename R, typename RX = R>
-dda_status matvec_device_impl(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, const cplx<RX> *scale,
-                              cplx<RX> *dots, hipStream_t s, const int *done, hipEvent_t *ev,
-                              const Work<R> *wk = nullptr) {
+// intermediates B1 / B2 of `wk` when given); x, y, scale and dots in RX.  EXT: leave out the lines
+// outside the planes' ranges of y.
+template <typename R, typename RX, bool EXT>
+dda_status matvec_passes(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, const cplx<RX> *scale, cplx<RX> *dots,
+                         hipStream_t s, const int *done, hipEvent_t *ev, const Work<R> &w) {
     using C = cplx<R>;
-    const Work<R> &w = wk ? *wk : work_of<R>(c);
     const C *tw = tw_of<R>(c);
     const C *gh = ghat_of<R>(c);
     const int ncomp = 3 * nrhs;
@@ -122,21 +110,22 @@ dda_status matvec_device_impl(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, 
     const size_t ly_bytes = (size_t)nly * lds_line_stride(c.Ly) * sizeof(C);
     const size_t lz_bytes = zmul_lds_elems(c.Lz) * sizeof(C);
     const int N = (int)c.N;
+    const int2 *ext = c.rows + (size_t)c.ny * c.nz;
+    const dim3 xg(ncomp * c.nz * ytiles), yg(ncomp * c.Lx * ztiles);
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[0], s));
-#define DDA_ARGS dim3(ncomp * c.nz * ytiles), dim3(nlx * c.pxf.tpl), lx_bytes, s, c.gmap, c.rows, c.gmap_stride, \
-                 c.rows_stride, x, w.B1, c.nx, c.ny, c.nz, N, \
-                 c.pxf, tw, tl.lnl_x, done
-#define DDA_BYTES lx_bytes
-    DDA_DISPATCH_X(c.Lx, k_fwd_x, DDA_BYTES, DDA_ARGS)
-#undef DDA_BYTES
-#undef DDA_ARGS
+#define fwd_x(L)                                                                                                     \
+    allow_lds(&k_fwd_x<R, L, RX, EXT>, lx_bytes);                                                                    \
+    hipLaunchKernelGGL((k_fwd_x<R, L, RX, EXT>), xg, dim3(nlx * c.pxf.tpl), lx_bytes, s, c.gmap, c.rows, ext,        \
+                       c.gmap_stride, c.rows_stride, x, w.B1, c.nx, c.ny, c.nz, N, c.pxf, tw, tl.lnl_x, done);
+    DDA_DISPATCH(c.Lx, fwd_x)
+#undef fwd_x
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[1], s));
-#define DDA_ARGS dim3(ncomp * c.Lx * ztiles), dim3(nly * c.pyf.tpl), ly_bytes, s, w.B1, w.B2, c.ny, c.nz, c.Lx, ncomp, \
-                 c.pyf, tw, tl.lnl_y, done
-#define DDA_BYTES ly_bytes
-    DDA_DISPATCH(c.Ly, k_fwd_y, DDA_BYTES, DDA_ARGS)
-#undef DDA_BYTES
-#undef DDA_ARGS
+#define fwd_y(L)                                                                                                     \
+    allow_lds(&k_fwd_y<R, L, EXT>, ly_bytes);                                                                        \
+    hipLaunchKernelGGL((k_fwd_y<R, L, EXT>), yg, dim3(nly * c.pyf.tpl), ly_bytes, s, ext, c.rows_stride, w.B1, w.B2, \
+                       c.ny, c.nz, c.Lx, ncomp, c.pyf, tw, tl.lnl_y, done);
+    DDA_DISPATCH(c.Ly, fwd_y)
+#undef fwd_y
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[2], s));
     const int zblocks = (c.Lx / 2 + 1) * (c.Ly / 2 + 1);  // one block per octant column
     switch (c.Lz) {
@@ -148,23 +137,40 @@ dda_status matvec_device_impl(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, 
             break;
     }
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[3], s));
-#define DDA_ARGS dim3(ncomp * c.Lx * ztiles), dim3(nly * c.pyi.tpl), ly_bytes, s, w.B2, w.B1, c.ny, c.nz, c.Lx, ncomp, \
-                 c.pyi, tw, tl.lnl_y, done
-#define DDA_BYTES ly_bytes
-    DDA_DISPATCH(c.Ly, k_inv_y, DDA_BYTES, DDA_ARGS)
-#undef DDA_BYTES
-#undef DDA_ARGS
+#define inv_y(L)                                                                                                     \
+    allow_lds(&k_inv_y<R, L, EXT>, ly_bytes);                                                                        \
+    hipLaunchKernelGGL((k_inv_y<R, L, EXT>), yg, dim3(nly * c.pyi.tpl), ly_bytes, s, ext, c.rows_stride, w.B2, w.B1, \
+                       c.ny, c.nz, c.Lx, ncomp, c.pyi, tw, tl.lnl_y, done);
+    DDA_DISPATCH(c.Ly, inv_y)
+#undef inv_y
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[4], s));
-#define DDA_ARGS dim3(ncomp * c.nz * ytiles), dim3(nlx * c.pxi.tpl), lx_bytes, s, c.gmap, c.rows, c.gmap_stride, \
-                 c.rows_stride, w.B1, x, y, c.nx, c.ny, c.nz, \
-                 N, c.pxi, tw, tl.lnl_x, scale, dots, done
-#define DDA_BYTES lx_bytes
-    DDA_DISPATCH_X(c.Lx, k_inv_x, DDA_BYTES, DDA_ARGS)
-#undef DDA_BYTES
-#undef DDA_ARGS
+#define inv_x(L)                                                                                                     \
+    allow_lds(&k_inv_x<R, L, RX, EXT>, lx_bytes);                                                                    \
+    hipLaunchKernelGGL((k_inv_x<R, L, RX, EXT>), xg, dim3(nlx * c.pxi.tpl), lx_bytes, s, c.gmap, c.rows, ext,        \
+                       c.gmap_stride, c.rows_stride, w.B1, x, y, c.nx, c.ny, c.nz, N, c.pxi, tw, tl.lnl_x, scale,    \
+                       dots, done);
+    DDA_DISPATCH(c.Lx, inv_x)
+#undef inv_x
     if (ev) DDA_HIP_CHECK(hipEventRecord(ev[5], s));
     DDA_HIP_CHECK(hipGetLastError());
     return DDA_OK;
+}
+
+// Lines (y, z) outside a plane's range of y are zero before the x pass and unused after it.  From 256 MB
+// of B1 on, the size of the last-level cache, they are left out of the x passes and of B1.  A sphere
+// leaves out 21 %: x passes 757 + 980 -> 677 + 896 us, y 1708 + 1670 -> 1622 + 1592 (256^3, two vectors);
+// 128^3, two vectors, 403 MB: 1166 -> 1150 us in all; a solve of a 64 x 64 x 64 grid's ellipsoid for 16
+// beams (402 MB) 50.0 -> 45.6 ms.  Below, the range is one more load before the
+// others: 48^3 72.3 -> 73.5, 160^3 in single precision (197 MB) 752 -> 759.
+template <typename R, typename RX = R>
+dda_status matvec_device_impl(Ctx &c, const cplx<RX> *x, cplx<RX> *y, int nrhs, const cplx<RX> *scale,
+                              cplx<RX> *dots, hipStream_t s, const int *done, hipEvent_t *ev,
+                              const Work<R> *wk = nullptr) {
+    const Work<R> &w = wk ? *wk : work_of<R>(c);
+    const size_t b1_bytes = (size_t)3 * nrhs * c.nz * c.Lx * row_pitch(c.ny) * sizeof(cplx<R>);
+    return b1_bytes >= ((size_t)256 << 20)
+               ? matvec_passes<R, RX, true>(c, x, y, nrhs, scale, dots, s, done, ev, w)
+               : matvec_passes<R, RX, false>(c, x, y, nrhs, scale, dots, s, done, ev, w);
 }
 
 }  // namespace dda

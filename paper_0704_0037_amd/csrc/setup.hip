@@ -345,10 +345,12 @@ template dda_status matvec_launch<float>(Ctx &, const float2 *, float2 *, int, c
 void destroy(Ctx *c);
 
 // Rows whose non-void cells form one run x0 <= x < x1 (or none) need no cell-map lookups in the x
-// passes: {x0 | x1 << 16, first dipole} per (y, z) row, x0 = 0xFFFF for a row of several runs.
+// passes: {x0 | x1 << 16, first dipole} per (y, z) row, x0 = 0xFFFF for a row of several runs.  After
+// the rows, per plane z, the range of y that holds dipoles: {y0 | y1 << 16, 0} (y0 = y1 = 0: none).
 static std::vector<int2> row_runs(const int32_t *gmap, int nx, int ny, int nz) {
-    std::vector<int2> rows((size_t)ny * nz);
-    for (size_t row = 0; row < rows.size(); ++row) {
+    const size_t nrow = (size_t)ny * nz;
+    std::vector<int2> rows(nrow + nz, make_int2(0, 0));
+    for (size_t row = 0; row < nrow; ++row) {
         const int32_t *g = gmap + row * nx;
         int x0 = -1, x1 = -1, runs = 0;
         for (int xx = 0; xx < nx; ++xx)
@@ -362,6 +364,11 @@ static std::vector<int2> row_runs(const int32_t *gmap, int nx, int ny, int nz) {
             rows[row] = make_int2(x0 | (x1 << 16), g[x0]);
         } else {
             rows[row] = make_int2(runs == 0 ? 0 : 0xFFFF, 0);
+        }
+        if (runs > 0) {
+            int2 &e = rows[nrow + row / ny];
+            const int y = (int)(row % ny);
+            e.x = (e.x ? e.x & 0xFFFF : y) | ((y + 1) << 16);
         }
     }
     return rows;
@@ -424,10 +431,10 @@ dda_status pack_setup(Ctx *const *members, int n, Ctx **out) {
     c->tw32 = donor->tw32;
     const size_t ncell = (size_t)box[0] * box[1] * box[2], nrow = (size_t)box[1] * box[2];
     c->gmap_stride = ncell;
-    c->rows_stride = nrow;
+    c->rows_stride = nrow + box[2];
     dda_status st = DDA_OK;
     std::vector<int32_t> gmap(ncell * n, -1);
-    std::vector<int2> rows(nrow * n);
+    std::vector<int2> rows(c->rows_stride * n);
     for (int i = 0; i < n; ++i) {
         const Ctx &m = *members[i];
         int32_t *g = gmap.data() + ncell * i;
@@ -437,7 +444,7 @@ dda_status pack_setup(Ctx *const *members, int n, Ctx **out) {
             g[((size_t)z * box[1] + y) * box[0] + x] = (int32_t)d;
         }
         const std::vector<int2> r = row_runs(g, box[0], box[1], box[2]);
-        std::copy(r.begin(), r.end(), rows.begin() + nrow * i);
+        std::copy(r.begin(), r.end(), rows.begin() + c->rows_stride * i);
     }
     if (hipStreamCreateWithFlags(&c->own_stream, hipStreamNonBlocking) != hipSuccess) {
         set_error("dda_solve_many: stream creation failed");
@@ -676,7 +683,7 @@ dda_status setup(Ctx **out, const int32_t grid[3], const uint8_t *mask, const do
         goto fail;
     }
     if ((st = device_alloc((void **)&c->gmap, ncell * sizeof(int32_t))) != DDA_OK) goto fail;
-    if ((st = device_alloc((void **)&c->rows, (size_t)c->ny * c->nz * sizeof(int2))) != DDA_OK) goto fail;
+    if ((st = device_alloc((void **)&c->rows, (size_t)(c->ny + 1) * c->nz * sizeof(int2))) != DDA_OK) goto fail;
     if ((st = device_alloc((void **)&c->lin, c->N * sizeof(int32_t))) != DDA_OK) goto fail;
     if ((st = device_alloc((void **)&c->tw64, total * sizeof(double2))) != DDA_OK) goto fail;
     if ((st = device_alloc((void **)&c->tw32, total * sizeof(float2))) != DDA_OK) goto fail;
