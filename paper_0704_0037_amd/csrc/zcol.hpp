@@ -131,6 +131,11 @@ template <typename R> constexpr bool zcol_fence(int L) {
     return sizeof(R) == 4 ? L > 128 : zcol_waves_per_simd<R>(L) == 3;
 }
 
+// lengths that load the first columns before the tensor is staged: there a block has one round and the
+// pass is a chain of latencies (32: a product of 25.3 -> 23.8 us; 48 with two vectors 13.7 -> 13.7, 64
+// 15.2 -> 15.5 us with the time to launch)
+constexpr bool zcol_ahead(int L) { return L <= 32; }
+
 template <typename R, int LC>
 __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
     k_zcol(cplx<R> *__restrict__ B2, const cplx<R> *__restrict__ Gh, int nz, int Lx, int Ly, int nrhs, int opb,
@@ -157,7 +162,7 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
     const int items = nocc * nrhs * 4;
     struct Item {
         C *col;
-        int mir, o;
+        int mir, o, rhs;
         bool ok;
     };
     auto item_at = [&](int it) {
@@ -168,7 +173,8 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
         const int oct = oct0 + m.o, kxo = oct % hx1, kyo = oct / hx1;
         const bool mxs = m.mir & 1, mys = m.mir & 2;
         m.ok = slot < CPW && it < items && (!mxs || (kxo != 0 && 2 * kxo != Lx)) &&
-               (!mys || (kyo != 0 && 2 * kyo != Ly)) && !(done && done[rhs < nrhs ? rhs : 0]);
+               (!mys || (kyo != 0 && 2 * kyo != Ly));
+        m.rhs = rhs < nrhs ? rhs : 0;
         const int kx = m.ok && mxs ? Lx - kxo : kxo, ky = m.ok && mys ? Ly - kyo : kyo;
         m.col = B2 + (((size_t)kx * (3 * nrhs) + rhs * 3) * Ly + ky) * nzp;
         return m;
@@ -188,6 +194,10 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
                     v[c][b * R0 + r] = m.ok && i < nz ? ld_stream(&m.col[c * cstride + i]) : czero<C>();
                 }
     };
+    // short lines: the first columns are on their way while the block stages the tensor (they do not
+    // wait for done either)
+    Item m = item_at(wave * CPW + slot);
+    if constexpr (zcol_ahead(LC)) load_column(m, j0);
     {   // the tensor columns and the twiddles of the block.  fp32 keeps eight loads of a thread in
         // flight (L = 256: 136 -> 128 us, 512: 999 -> 895 us); fp64, with half the waves, is 0-2 %
         // faster loading one by one
@@ -207,7 +217,9 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
     __syncthreads();
     if (slot >= CPW) return;
     for (int it0 = wave * CPW; it0 < items; it0 += W * CPW) {
-        const Item m = item_at(it0 + slot);
+        const bool ahead = zcol_ahead(LC) && it0 == wave * CPW;
+        if (!ahead) m = item_at(it0 + slot);
+        m.ok = m.ok && !(done && done[m.rhs]);
         if (!__any(m.ok)) continue;
         // opaque from round to round: the LDS addresses are formed inside each round instead of being
         // held in registers across rounds
@@ -220,7 +232,7 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
         const C *g = gsh + m.o * 6 * HZ1;
         const bool ok = m.ok;
         C *col = m.col;
-        load_column(m, j);
+        if (!ahead) load_column(m, j);
         // forward passes
         static_for<0, NP>([&](auto pc) {
             constexpr int p = decltype(pc)::value, Rp = Z::F.radix[p], Ns = Z::F.ns[p], NB = Z::NB(Rp), nb = LC / Rp;
