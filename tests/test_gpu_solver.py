@@ -883,9 +883,10 @@ def test_farfield_in_rings_about_an_axis(axis, rings):
 
 
 @pytest.mark.parametrize("solver", ["QMR", "BICG", "BICGSTAB"])
-@pytest.mark.parametrize("n", [1, 341, 342, 87381, 87382, (40, 40, 2)])
+@pytest.mark.parametrize("n", [1, 341, 342, 10922, 10923, 87381, 87382, (40, 40, 2)])
 def test_scalars_formed_in_the_vector_kernels(solver, n):
-    """Particles on both sides of one block and of 256 blocks of partial sums (one per thread of the
+    """Particles on both sides of one, 32 (up to which QMR closes an iteration in the next one) and 256 blocks
+    of partial sums (one per thread of the
     block that adds them): the history falls to the tolerance, the residual of the
     returned vector is the last one of the history (recursive and true residuals part by rounding and the
     iterations' growth of it, far below the tolerance of 1e-7), and a second right-hand side that is
@@ -895,7 +896,7 @@ def test_scalars_formed_in_the_vector_kernels(solver, n):
     if isinstance(n, tuple):
         mask = np.ones(n, np.uint8)
     else:
-        side = 8 if n < 400 else 48
+        side = 8 if n < 400 else 23 if n < 20000 else 48
         mask = np.zeros(side ** 3, np.uint8)
         mask[:n] = 1
         mask = mask.reshape(side, side, side)
