@@ -52,7 +52,7 @@ def kernel_sources_digest():
     """Digest of the matvec kernel sources, to tell whether recorded byte counters still apply."""
     import hashlib
     d = hashlib.sha256()
-    for f in ("fft.hpp", "matvec_kernels.hpp", "matvec_launch.hpp", "common.hpp"):
+    for f in ("fft.hpp", "matvec_kernels.hpp", "matvec_launch.hpp", "zcol.hpp", "common.hpp"):
         with open(os.path.join(ROOT, "paper_0704_0037_amd", "csrc", f), "rb") as fh:
             d.update(fh.read())
     return d.hexdigest()[:16]

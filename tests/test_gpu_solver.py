@@ -885,13 +885,12 @@ def test_farfield_in_rings_about_an_axis(axis, rings):
 @pytest.mark.parametrize("solver", ["QMR", "BICG", "BICGSTAB"])
 @pytest.mark.parametrize("n", [1, 341, 342, 10922, 10923, 87381, 87382, (40, 40, 2)])
 def test_scalars_formed_in_the_vector_kernels(solver, n):
-    """Particles on both sides of one, 32 (up to which QMR closes an iteration in the next one) and 256 blocks
-    of partial sums (one per thread of the
-    block that adds them): the history falls to the tolerance, the residual of the
-    returned vector is the last one of the history (recursive and true residuals part by rounding and the
-    iterations' growth of it, far below the tolerance of 1e-7), and a second right-hand side that is
-    done before the first iteration keeps its vector.  The flat box, at one row a block, has
-    more partial sums of the product (4,800) than every block adds by itself."""
+    """Particles on both sides of one, 32 (up to which QMR closes an iteration in the next one) and 256
+    blocks of partial sums (one per thread of the block that adds them): the history falls to the
+    tolerance, the residual of the returned vector is the last one of the history (recursive and true
+    residuals part by rounding and the iterations' growth of it, far below the tolerance of 1e-7), and a
+    second right-hand side that is done before the first iteration keeps its vector.  The flat box, at
+    one row a block, has more partial sums of the product (4,800) than every block adds by itself."""
     dda = _dda()
     if isinstance(n, tuple):
         mask = np.ones(n, np.uint8)
@@ -912,3 +911,27 @@ def test_scalars_formed_in_the_vector_kernels(solver, n):
         h = info[0]["res_hist"]
         assert len(h) == info[0]["iters"] + 1 and h[-1] < 1e-7 <= min(h[:-1])
         assert abs(r.item() - h[-1]) < 1e-9
+
+
+def test_packed_batch_with_ranges_of_its_particles():
+    """Eleven particles in one batch of more than 256 MB of intermediates, each with y ranges of its own
+    per plane (and planes without dipoles): every solution meets its tolerance of 1e-10 and is that of the
+    particle alone (two solutions at that tolerance, m = 1.2: within 1e-8 as in the smaller batches)."""
+    dda = _dda()
+    shapes = [inputs.sphere_mask(64)]
+    for i in range(10):
+        e = inputs.ellipsoid_mask((64, 40 + 2 * i, 64 - 4 * i), (32 - i, 20 + i, 30 - 2 * i))
+        e[3 + i] = 0
+        shapes.append(e)
+    beams = inputs.beams_for_orientations(len(shapes), seed=3)[:len(shapes)]
+    ctxs = [dda.Context(mk, 1.2 + 0.01j, 0.2, pad=(128, 128, 128)) for mk in shapes]
+    try:
+        xs, infos, st = dda.solve_many(ctxs, beams, tol=1e-10, pack=True)
+        assert st == 0
+        for c, b, x, inf in zip(ctxs, beams, xs, infos):
+            x1, _, st = c.solve([b], tol=1e-10)
+            assert st == 0 and inf["status"] == 0 and inf["res_true"] < 2e-10
+            assert (x - x1[0]).abs().max() < 1e-8 * x1.abs().max()
+    finally:
+        for c in ctxs:
+            c.close()
