@@ -5,9 +5,9 @@
 
 #include <algorithm>
 #include <cmath>
+#include <map>
 #include <mutex>
-#include <set>
-#include <tuple>
+#include <utility>
 
 #include "ctx.hpp"
 #include "matvec_kernels.hpp"
@@ -23,18 +23,22 @@ template <typename R> inline const cplx<R> *ghat_of(const Ctx &c);
 template <> inline const double2 *ghat_of<double>(const Ctx &c) { return c.ghat; }
 template <> inline const float2 *ghat_of<float>(const Ctx &c) { return c.ghat32; }
 
-// blocks above 64 KiB of dynamic LDS must be allowed explicitly; done once per kernel, device and
-// size, so that launches recorded into a graph later make no attribute calls
+// blocks above 64 KiB of dynamic LDS must be allowed explicitly.  The attribute is the kernel's limit and
+// stays as it was set last, while one kernel runs with several sizes (the column kernel's follow the grid
+// and the number of vectors), so it is only ever raised: once per kernel, device and larger size, and
+// launches recorded into a graph after an eager one of the same size make no attribute calls.
 template <class K> inline void allow_lds(K kernel, size_t bytes) {
     if (bytes <= 64 * 1024) return;
     static std::mutex mu;
-    static std::set<std::tuple<const void *, int, size_t>> seen;
+    static std::map<std::pair<const void *, int>, size_t> allowed;
     int dev = 0;
     (void)hipGetDevice(&dev);
     const void *f = reinterpret_cast<const void *>(kernel);
     std::lock_guard<std::mutex> lock(mu);
-    if (seen.insert(std::make_tuple(f, dev, bytes)).second)
-        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    size_t &most = allowed[{f, dev}];
+    if (bytes <= most) return;
+    most = bytes;
+    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 // LAUNCH(L) for a length with specialized kernels, LAUNCH(0) (planned at run time) for the others

@@ -1,0 +1,52 @@
+"""Host-side launch rules of the kernels, compiled alone for the CPU: no GPU call is made."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_0704_0037_amd", "csrc")
+
+
+def _run(tmp_path, text):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    src, exe = tmp_path / "probe.hip", tmp_path / "probe"
+    src.write_text(text)
+    subprocess.run([hipcc, "--offload-host-only", "-O0", "-std=c++17", "-Wno-everything", "-I", CSRC, "-I",
+                    os.path.join(CSRC, "..", "..", "include"), str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
+
+
+def test_lds_limit_of_a_kernel_is_never_lowered(tmp_path):
+    """The column kernel's dynamic LDS follows the grid and the number of vectors (L = 256: 78,240 and
+    65,856 bytes), and the limit set for a kernel is the last one set: whatever the order of the calls,
+    the limit at every launch covers that launch."""
+    out = _run(tmp_path, """
+#include <hip/hip_runtime.h>
+#include <cstdio>
+static int limit = 65536;
+static hipError_t set_limit(const void *, hipFuncAttribute, int v) { limit = v; return hipSuccess; }
+static hipError_t device(int *d) { *d = 0; return hipSuccess; }
+#define hipFuncSetAttribute set_limit
+#define hipGetDevice device
+#include "matvec_launch.hpp"
+namespace dda { void set_error(const std::string &) {} }
+static void kernel() {}
+int main() {
+    using namespace dda;
+    auto size = [](int noct, int n) {
+        const ZShape z = zcol_shape<double, 256>(noct, n);
+        return zcol_lds<double, 256>(z.opb, z.W);
+    };
+    const size_t a = size(1285, 5), b = size(257 * 257, 9);
+    for (size_t bytes : {a, b, a, b, (size_t)1024, a}) {
+        allow_lds(&kernel, bytes);
+        std::printf("%zu %d\\n", bytes, limit);
+    }
+}
+""")
+    pairs = [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
+    assert len({b for b, _ in pairs if b > 65536}) == 2  # two sizes above the default limit
+    assert all(b <= lim for b, lim in pairs), pairs
