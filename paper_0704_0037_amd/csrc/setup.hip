@@ -670,7 +670,8 @@ dda_status setup(Ctx **out, const int32_t grid[3], const uint8_t *mask, const do
     };
     const bool tiles_ok = tiles(c->tl64, 16, max_threads<double>()) && tiles(c->tl32, 8, max_threads<float>());
     c->nc_z = 1;
-    if (3 * zmul_ct(c->pzf) > DDA_ZMUL_THREADS || zmul_lds_elems(c->Lz) * 16 > 160 * 1024 || !tiles_ok) {
+    // a z line runs in at most one wave of lanes (longer ones would leave k_zmul no column slot)
+    if (zmul_tpl(c->pzf) > 64 || 3 * zmul_ct(c->pzf) > DDA_ZMUL_THREADS || zmul_lds_elems(c->Lz) * 16 > 160 * 1024 || !tiles_ok) {
         set_error("dda_setup: padded size too large for one workgroup per line");
         delete c;
         return DDA_EINVAL;

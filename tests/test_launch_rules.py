@@ -50,3 +50,28 @@ int main() {
     pairs = [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
     assert len({b for b, _ in pairs if b > 65536}) == 2  # two sizes above the default limit
     assert all(b <= lim for b, lim in pairs), pairs
+
+
+def _setup(grid, pad, mask=None):
+    """Status and message of a dda_setup call that is to end before any device call."""
+    import ctypes as ct
+
+    from paper_0704_0037_amd import dda
+    L = dda.lib()
+    L.dda_last_error.restype = ct.c_char_p
+    h = ct.c_void_p()
+    cells = (ct.c_uint8 * (grid[0] * grid[1] * grid[2]))(1)
+    opts = dda.SetupOpts()
+    opts.pad[:] = pad
+    st = L.dda_setup(ct.byref(h), (ct.c_int32 * 3)(*grid), cells, (ct.c_double * 2)(1.5, 0.0), 0.4, 0, ct.byref(opts), None)
+    assert h.value is None
+    return st, L.dda_last_error()
+
+
+@pytest.mark.parametrize("pad", [405, 486, 540, 600, 1024, 4096])
+def test_z_lines_wider_than_a_wave_are_refused(pad):
+    """L / (largest radix) > 64 lanes leaves the z pass no slot for a column: refused before any device
+    call (405 and 486 have no radix 8, the others are longer than 512)."""
+    from paper_0704_0037_amd import dda
+    st, why = _setup((2, 2, 100), (4, 4, pad))
+    assert st == dda.EINVAL and b"padded size too large" in why
