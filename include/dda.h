@@ -168,7 +168,7 @@ typedef struct {
  * dda_setup — build a context for one particle (Sec. 2: grid of dipoles, non-void list,
  * polarizability, Fourier transform of the interaction matrix).
  *   out    receives the context (set to NULL on failure)
- *   grid   {nx, ny, nz}, each 1..2048
+ *   grid   {nx, ny, nz}, each 1..2048, nz at most 256 (the z pass runs padded lengths up to 512)
  *   mask   host uint8 [nz][ny][nx]; at least one nonzero cell
  *   m      {Re m, Im m}, refractive index of the (homogeneous) material
  *   kd     wavenumber times dipole size, > 0

@@ -74,15 +74,21 @@ static bool five_smooth(int L) {
 // Padded length of an axis of n cells: at least 2n - 1 (the circulant embedding of the Toeplitz
 // interaction), 5-smooth, with at most 64 threads per line in the z pass (one column of three
 // lines per block; zmul_tpl); a length with compile-time specialized kernels is preferred when it
-// costs at most 25 % more than the smallest admissible one.
-static bool admissible(int L) {
+// costs at most 25 % more than the smallest admissible one.  No length above 512 meets the z pass's
+// limit: longer axes get the smallest length that the x and y passes run (dda_setup refuses it along z).
+constexpr int kMaxPad = 4096;
+static bool admissible(int L, int max_tpl) {
     if (!five_smooth(L)) return false;
     const FftPlan p = make_plan(L, kMaxRadixZ, false);
-    return p.npass > 0 && zmul_tpl(p) <= 64;
+    return p.npass > 0 && (max_tpl > 64 ? p.tpl : zmul_tpl(p)) <= max_tpl;
 }
 static int smallest_pad(int n) {
-    int L = std::max(1, 2 * n - 1);
-    while (!admissible(L)) ++L;
+    static_assert(kMaxRadix == kMaxRadixZ, "one plan serves the passes of all axes");
+    const int least = n > kMaxPad / 2 ? kMaxPad : std::max(1, 2 * n - 1);  // dda_setup takes at most 2048 cells
+    int L = least;
+    while (L < kMaxPad && !admissible(L, 64)) ++L;
+    if (!admissible(L, 64))
+        for (L = least; L < kMaxPad && !admissible(L, max_threads<double>());) ++L;
 #define DDA_SPEC_ITEM(S) S,
     static const int spec[] = {DDA_SPECIALIZED_LENGTHS(DDA_SPEC_ITEM)};
 #undef DDA_SPEC_ITEM
@@ -605,7 +611,7 @@ dda_status setup(Ctx **out, const int32_t grid[3], const uint8_t *mask, const do
     for (int a = 0; a < 3; ++a) {
         const int want = opts ? opts->pad[a] : 0;
         if (want > 0) {
-            if (want < 2 * n[a] - 1 || !five_smooth(want) || want > 4096) {
+            if (want < 2 * n[a] - 1 || !five_smooth(want) || want > kMaxPad) {
                 set_error("dda_setup: padded size must be >= 2n-1, 5-smooth and <= 4096");
                 delete c;
                 return DDA_EINVAL;

@@ -387,3 +387,18 @@ def test_ranges_of_planes_in_single_precision():
         y = ctx.matvec(inputs.X_POL, x)
         yf = ctx.matvec_f32(inputs.X_POL, x.to(torch.complex64))
         assert (yf.to(torch.complex128) - y).norm() < 1e-5 * y.norm()
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+def test_axes_longer_than_256_cells_by_default(axis):
+    """257 cells along x or y take the padded length 540 (432 threads of four lines a block) by themselves;
+    bar of the other products: 1e-12 of fp64 rounding."""
+    dda = _dda()
+    n = [2, 2, 2]
+    n[axis] = 257
+    mask = _random_mask(n[::-1], 41 + axis, 0.8)  # [nz][ny][nx]
+    with dda.Context(mask, 1.4 + 0.02j, 0.5) as ctx:
+        assert ctx.padded_grid()[axis] == 540
+        x = inputs.random_vector(ctx.n, seed=6)
+        y = ctx.matvec(inputs.X_POL, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert _rel_err(y, _oracle_y(mask, 1.4 + 0.02j, 0.5, inputs.X_POL, x)) < 1e-12

@@ -75,3 +75,25 @@ def test_z_lines_wider_than_a_wave_are_refused(pad):
     from paper_0704_0037_amd import dda
     st, why = _setup((2, 2, 100), (4, 4, pad))
     assert st == dda.EINVAL and b"padded size too large" in why
+
+
+@pytest.mark.timeout(60, method="thread")
+@pytest.mark.parametrize("nz", [257, 300, 2047, 2048])
+def test_default_padding_ends_for_long_axes(nz):
+    """No padded length above 512 fits the z pass: more than 256 cells along z are refused, not searched
+    for without end."""
+    from paper_0704_0037_amd import dda
+    st, why = _setup((2, 3, nz), (0, 0, 0))
+    assert st == dda.EINVAL and b"padded size too large" in why
+
+
+@pytest.mark.timeout(60, method="thread")
+@pytest.mark.parametrize("n,length", [(1, 1), (16, 32), (93, 192), (97, 200), (256, 512), (257, 540), (270, 540),
+                                      (547, 1125), (1094, 2250), (2047, 4096), (2048, 4096), (2049, 4096), (1 << 30, 4096)])
+def test_default_padded_length(n, length):
+    """Up to 256 cells the lengths chosen before; above, the smallest 5-smooth length of at least 2n - 1 whose
+    L / (largest radix) is at most 512 (1094 cells: 2187 = 3^7 has 729, 2250 = 6 5 5 5 3 has 375)."""
+    import ctypes
+
+    from paper_0704_0037_amd import dda
+    assert getattr(dda.lib(), "_ZN3dda11default_padEi")(ctypes.c_int(n)) == length
