@@ -155,6 +155,25 @@ template <typename R> inline size_t dots_per_rhs(const Ctx &c) {
     return (size_t)3 * c.nz * ((c.ny + t.nl_x - 1) / t.nl_x);
 }
 
+// Whether QMR closes an iteration in the next one's first vector kernel, which saves a launch per
+// iteration, but runs one product more than needed for a right-hand side that stops: where that
+// product is short.  nb: blocks of a vector kernel.  At most 32 of them (10,922 dipoles), and one
+// vector, or lengths with compile-time plans (others take twice as long) and at most 450,000 padded
+// cells in all vectors.  A solve without and with it, in turn:
+//   one vector, 2,176 dipoles (32^3), 39 iterations 3082 and 2838 us; 912 (24^3, no such plan), 5: 662, 672
+//   442,368 cells: 2 vectors on 60^3, 8 and 34 iterations 836 and 838, 3655 and 3432; 4 on 48^3, 7: 760, 760
+//   above: 8 on 48^3, 7 iterations 939 and 958; 8 on 60^3, 8: 1398 and 1466; 8 on 24^3, 5: 1110 and 1185;
+//   64 on 15^3, 5: 3773 and 4282
+inline bool qmr_closes_late(int nb, int nrhs, int Lx, int Ly, int Lz) {
+    auto planned = [](int L) {
+#define DDA_SPEC_ITEM(S) || L == S
+        return false DDA_SPECIALIZED_LENGTHS(DDA_SPEC_ITEM);
+#undef DDA_SPEC_ITEM
+    };
+    return nb <= 32 && (nrhs == 1 || (planned(Lx) && planned(Ly) && planned(Lz) &&
+                                      (double)nrhs * Lx * Ly * Lz <= 450000.0));
+}
+
 dda_status device_alloc(void **p, size_t bytes);
 // a small host table to device memory, ordered on stream s, without waiting for it
 dda_status put_table(void *dst, const void *src, size_t bytes, hipStream_t s);

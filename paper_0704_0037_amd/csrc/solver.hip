@@ -238,11 +238,8 @@ __device__ __forceinline__ bool qmr_close(SolveState &S, double r2) {
     return true;
 }
 
-// Particles of at most 32 blocks (10,922 dipoles) leave the end of an iteration to the first vector kernel
-// of the next one (CLOSE), except the last of a chunk: 68.8 -> 64.4 us an iteration at 2,176 dipoles, a
-// solve of 4 iterations at 7,208 602 -> 560, of 33 2683 -> 2450.  A right-hand side that stops has then
-// run one more product than it needed: 23 iterations of 8 vectors at 14,328 dipoles 3497 -> 3532 us.
-constexpr int kCloseBlocks = 32;
+// Small products leave the end of an iteration to the first vector kernel of the next one (CLOSE; the
+// rule is qmr_closes_late), except the last of a chunk.
 
 // eps = p^T A p; beta = eps / delta; vt = pt - (beta / rho) vt; partials |vt|^2, vt^T vt
 template <typename R, bool CLOSE>
@@ -1229,7 +1226,7 @@ template <typename R> static dda_status enqueue_iterations(Run<R> &k, int count)
         } else if (k.solver == DDA_QMR) {
             if ((st = run_matvec(k, v.p, v.pt, w.dots, B.done)) != DDA_OK) return st;
             sum_dots_first();
-            const bool merge = B.nb <= kCloseBlocks;
+            const bool merge = qmr_closes_late(B.nb, nrhs, c.Lx, c.Ly, c.Lz);
             hipLaunchKernelGGL((merge && it > 0 ? k_qmr_vt<R, true> : k_qmr_vt<R, false>), vg, vb, 0, s, B.st, B.done,
                                v.pt, v.vt, n3, B.part, w.dots, ndots, dsum, B.part2, B.st2, B.hist, B.hcap);
             hipLaunchKernelGGL(k_qmr_update<R>, vg, vb, 0, s, B.st, B.done, v.p, v.pt, v.vt, v.d, v.s, x, v.r, n3,

@@ -97,3 +97,18 @@ def test_default_padded_length(n, length):
 
     from paper_0704_0037_amd import dda
     assert getattr(dda.lib(), "_ZN3dda11default_padEi")(ctypes.c_int(n)) == length
+
+
+def test_qmr_closes_late_only_where_a_product_is_short(tmp_path):
+    """The extra product of a right-hand side that stops is short for one vector and for few vectors on
+    specialized lengths; elsewhere it costs more than the launches it saves (measured beside the rule)."""
+    out = _run(tmp_path, """
+#include <cstdio>
+#include "ctx.hpp"
+int main() {
+    const int c[][4] = {{1, 1, 24, 32}, {32, 1, 60, 64}, {7, 8, 32, 32}, {31, 2, 60, 60}, {22, 4, 48, 48},
+                        {33, 1, 64, 64}, {22, 8, 48, 48}, {31, 8, 60, 60}, {1, 64, 15, 15}, {3, 2, 24, 32}, {3, 2, 32, 24}};
+    for (auto &q : c) std::printf("%d ", (int)dda::qmr_closes_late(q[0], q[1], q[2], q[2], q[3]));
+}
+""")
+    assert out == ["1"] * 5 + ["0"] * 6
