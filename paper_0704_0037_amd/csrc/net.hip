@@ -392,24 +392,24 @@ __global__ void __launch_bounds__(256) k_wgrad(const bf16 *__restrict__ gr, cons
 // neighbour words.  Bound by the staging (every voxel transposed with two-byte granularity); at 48^3,
 // batch 8, 16 x 16 channels 389 -> 30 us, 32 -> 16 up 494 -> 60 us (one tap per block before, which staged
 // gradient and input 27 times; 42 and 75 us without the next planes' loads in flight).
-template <int CIN, int COUT, bool UP>
+// MANY: a large batch has more tiles (rows, z chunks and particles) than blocks, and a block takes
+// several neighbouring ones into the same sums; otherwise a block is a tile.
+template <int CIN, int COUT, bool UP, bool MANY>
 __global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr, const bf16 *__restrict__ in, int g,
-                                                    int zchunk, float *__restrict__ part, float *__restrict__ bpart) {
+                                                    int zchunk, int ntile, float *__restrict__ part,
+                                                    float *__restrict__ bpart) {
     extern __shared__ __align__(16) unsigned char smem_wg[];
-    const int t = threadIdx.x, lane = t & 63, dz = t >> 6, kg = lane >> 4, ch = lane & 15;
+    int t = threadIdx.x;
+    const int lane = t & 63, dz = t >> 6, kg = lane >> 4, ch = lane & 15;
     const int ci0 = (blockIdx.y % (CIN / 16)) * 16, co0 = (blockIdx.y / (CIN / 16)) * 16;
     const int gi = UP ? g / 2 : g;
     const int xp = g + 24;             // pitch of one channel's row: 8 before, the voxels, 16 after (16-byte rows, skewed banks)
     const int rowp = 16 * xp;          // one row of 16 channels
     bf16 *xs = reinterpret_cast<bf16 *>(smem_wg);  // [3][6][16][xp]
     bf16 *gs = xs + 18 * rowp;                     // [4][16][xp]
-    int blk = blockIdx.x;
     const int ytiles = g / 4, ztiles = (g + zchunk - 1) / zchunk;
-    const int y0 = (blk % ytiles) * 4;
-    blk /= ytiles;
-    const int z0 = (blk % ztiles) * zchunk, z1 = min(g, z0 + zchunk), b = blk / ztiles;
-    const bf16 *inb = in + (size_t)b * gi * gi * gi * CIN + ci0;
-    const bf16 *grb = gr + (size_t)b * g * g * g * COUT + co0;
+    int y0 = 0;
+    const bf16 *inb = in, *grb = gr;
     for (int e = t; e < 22 * rowp / 8; e += 192) reinterpret_cast<uint4 *>(xs)[e] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     // two neighbouring voxels' eight channels -> eight words [channel][x, x + 1]
@@ -465,45 +465,59 @@ __global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr,
     for (int k = 0; k < 9; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     Frag ones;
     ones.u = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-    fetch_in(z0 - 1);
-    put_in(0);
-    fetch_in(z0);
-    put_in(1);
-    fetch_in(z0 + 1);
-    fetch_g(z0);
-    for (int z = z0; z < z1; ++z) {
-        const int s0 = (z - z0) % 3, slot2 = s0 == 0 ? 2 : s0 - 1;
-        put_in(slot2);
-        put_g();
-        __syncthreads();
-        if (z + 1 < z1) {  // the next planes on their way during the products
-            fetch_in(z + 2);
-            fetch_g(z + 1);
-        }
-        const int sl = (s0 + dz) % 3;
-        const bf16 *xrow = xs + (sl * 6 + kg) * rowp + ch * xp;  // row of tap dy = -1
-        const bf16 *grow = gs + kg * rowp + ch * xp;
-        for (int x = 0; x < g; x += 8) {
-            Frag a;
-            a.u = *reinterpret_cast<const uint4 *>(grow + 8 + x);
-#pragma unroll
-            for (int dy = 0; dy < 3; ++dy) {
-                const bf16 *r = xrow + dy * rowp + 8 + x;
-                Frag c, l, h;
-                c.u = *reinterpret_cast<const uint4 *>(r);
-                const uint32_t pv = *reinterpret_cast<const uint32_t *>(r - 2), nx = *reinterpret_cast<const uint32_t *>(r + 8);
-                const uint32_t m1 = __builtin_amdgcn_alignbit(c.u.y, c.u.x, 16), m2 = __builtin_amdgcn_alignbit(c.u.z, c.u.y, 16),
-                               m3 = __builtin_amdgcn_alignbit(c.u.w, c.u.z, 16);
-                l.u = make_uint4(__builtin_amdgcn_alignbit(c.u.x, pv, 16), m1, m2, m3);  // voxels x - 1 .. x + 6
-                h.u = make_uint4(m1, m2, m3, __builtin_amdgcn_alignbit(nx, c.u.w, 16));  // voxels x + 1 .. x + 8
-                acc[3 * dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, l.v, acc[3 * dy], 0, 0, 0);
-                acc[3 * dy + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, c.v, acc[3 * dy + 1], 0, 0, 0);
-                acc[3 * dy + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, h.v, acc[3 * dy + 2], 0, 0, 0);
-            }
-            if (dz == 1 && ci0 == 0) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, bacc, 0, 0, 0);
-        }
-        __syncthreads();
+    int tile = blockIdx.x, last = tile;
+    if constexpr (MANY) {
+        tile = (int)((int64_t)blockIdx.x * ntile / gridDim.x);
+        last = (int)((int64_t)(blockIdx.x + 1) * ntile / gridDim.x) - 1;
     }
+    do {
+        // opaque from tile to tile: the staging addresses are formed in each instead of being held (which
+        // would take a third of the waves)
+        if constexpr (MANY) __asm__ volatile("" : "+v"(t));
+        y0 = (tile % ytiles) * 4;
+        const int q = tile / ytiles, z0 = (q % ztiles) * zchunk, z1 = min(g, z0 + zchunk), b = q / ztiles;
+        inb = in + (size_t)b * gi * gi * gi * CIN + ci0;
+        grb = gr + (size_t)b * g * g * g * COUT + co0;
+        fetch_in(z0 - 1);
+        put_in(0);
+        fetch_in(z0);
+        put_in(1);
+        fetch_in(z0 + 1);
+        fetch_g(z0);
+        for (int z = z0; z < z1; ++z) {
+            const int s0 = (z - z0) % 3, slot2 = s0 == 0 ? 2 : s0 - 1;
+            put_in(slot2);
+            put_g();
+            __syncthreads();
+            if (z + 1 < z1) {  // the next planes on their way during the products
+                fetch_in(z + 2);
+                fetch_g(z + 1);
+            }
+            const int sl = (s0 + dz) % 3;
+            const bf16 *xrow = xs + (sl * 6 + kg) * rowp + ch * xp;  // row of tap dy = -1
+            const bf16 *grow = gs + kg * rowp + ch * xp;
+            for (int x = 0; x < g; x += 8) {
+                Frag a;
+                a.u = *reinterpret_cast<const uint4 *>(grow + 8 + x);
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const bf16 *r = xrow + dy * rowp + 8 + x;
+                    Frag c, l, h;
+                    c.u = *reinterpret_cast<const uint4 *>(r);
+                    const uint32_t pv = *reinterpret_cast<const uint32_t *>(r - 2), nx = *reinterpret_cast<const uint32_t *>(r + 8);
+                    const uint32_t m1 = __builtin_amdgcn_alignbit(c.u.y, c.u.x, 16), m2 = __builtin_amdgcn_alignbit(c.u.z, c.u.y, 16),
+                                   m3 = __builtin_amdgcn_alignbit(c.u.w, c.u.z, 16);
+                    l.u = make_uint4(__builtin_amdgcn_alignbit(c.u.x, pv, 16), m1, m2, m3);  // voxels x - 1 .. x + 6
+                    h.u = make_uint4(m1, m2, m3, __builtin_amdgcn_alignbit(nx, c.u.w, 16));  // voxels x + 1 .. x + 8
+                    acc[3 * dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, l.v, acc[3 * dy], 0, 0, 0);
+                    acc[3 * dy + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, c.v, acc[3 * dy + 1], 0, 0, 0);
+                    acc[3 * dy + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, h.v, acc[3 * dy + 2], 0, 0, 0);
+                }
+                if (dz == 1 && ci0 == 0) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, bacc, 0, 0, 0);
+            }
+            __syncthreads();
+        }
+    } while (MANY && ++tile <= last);
     // D: rows (output channels) 4 kg + i, column (input channel) lane & 15
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
@@ -930,11 +944,15 @@ static dda_status conv(Net &n, int cin, int cout, bool upm, const bf16 *in, cons
     return DDA_OK;
 }
 
-// blocks of a layer's weight gradient: rows of four and z chunks where k_wgrad_rows takes the box
-// (about two blocks per compute unit over all channel tiles), else chunks of voxels
+// Blocks of a layer's weight gradient: rows of four and z chunks where k_wgrad_rows takes the box
+// (about two blocks per compute unit over all channel tiles), else chunks of voxels.  Each block writes
+// sums of its own, so their number is bounded: a block per tile up to twelve per compute unit over all
+// channel tiles (85 MB for any layer), beyond as many blocks as are resident (twelve waves per compute
+// unit by the registers, or by LDS), which share the tiles evenly.  A block per tile for any batch took
+// 255 MB for 256 boxes of 48^3, 7.2 GB for 65,536 of 8^3.
 struct WgradShape {
     bool rows;
-    int chunk, nblk;
+    int chunk, ntile, nblk;
 };
 static WgradShape wgrad_shape(const LayerDef &d, int g, int batch) {
     WgradShape w;
@@ -944,10 +962,12 @@ static WgradShape wgrad_shape(const LayerDef &d, int g, int batch) {
         const int per_z = batch * (g / 4), pairs = d.pcin / 16 * (d.pcout / 16);
         const int zt = std::max(1, std::min(g / 4, 512 / std::max(1, per_z * pairs)));
         w.chunk = (g + zt - 1) / zt;
-        w.nblk = per_z * ((g + w.chunk - 1) / w.chunk);
+        w.ntile = per_z * ((g + w.chunk - 1) / w.chunk);
+        const int resident = 256 * std::min<int>(4, 160 * 1024 / (int)wgrad_rows_lds(g));
+        w.nblk = w.ntile <= 3072 / pairs ? w.ntile : resident / pairs;
     } else {
         w.chunk = chunk_of(nv);
-        w.nblk = (int)((nv + w.chunk - 1) / w.chunk);
+        w.ntile = w.nblk = (int)((nv + w.chunk - 1) / w.chunk);
     }
     return w;
 }
@@ -967,8 +987,8 @@ static dda_status wgrad(Net &n, int l, const bf16 *g, const bf16 *in, int gside,
 #define DNET_WG(CI, CO, UPM)                                                                                        \
     if (!done && d.pcin == CI && d.pcout == CO && (d.kind == 2) == UPM) {                                           \
         if (w.rows)                                                                                                 \
-            hipLaunchKernelGGL((k_wgrad_rows<CI, CO, UPM>), rgrid, dim3(192), lds, s, g, in, gside, w.chunk, n.part, \
-                               n.bpart);                                                                            \
+            hipLaunchKernelGGL((w.nblk < w.ntile ? k_wgrad_rows<CI, CO, UPM, true> : k_wgrad_rows<CI, CO, UPM, false>), \
+                               rgrid, dim3(192), lds, s, g, in, gside, w.chunk, w.ntile, n.part, n.bpart);          \
         else                                                                                                        \
             hipLaunchKernelGGL((k_wgrad<CI, CO, UPM>), dim3(w.nblk, 27), dim3(256), 0, s, g, in, gside, nvi, w.chunk, \
                                n.part, n.bpart);                                                                    \

@@ -186,3 +186,44 @@ def test_boxes_on_both_sides_of_the_tiled_kernels(G, B, grad):
             a, b = g[off:off + n].astype(np.float64), go[off:off + n]
             assert np.linalg.norm(a - b) <= 3e-2 * np.linalg.norm(b) + 1e-12, (li, n)
             off += n
+
+
+def test_memory_of_large_batches_is_the_tensors():
+    """The weight gradient's partial sums do not grow with the batch: 4,096 more particles of 8^3 cells take
+    the network's tensors (292 bytes a cell: 16 to 64 channels in bfloat16 on four levels) and no 110 KB each
+    for sums of their own (a quarter is left for rounding by the allocator)."""
+    dda = _dda()
+    p = _params(7)
+    used = []
+    for B in (4096, 8192):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        with dda.Net(8, p, max_batch=B):
+            used.append(before - torch.cuda.mem_get_info()[0])
+    assert used[1] - used[0] < 1.25 * 4096 * 512 * 292
+
+
+@pytest.mark.parametrize("G,B", [(8, 2048), (16, 512), (24, 384)])
+def test_blocks_that_take_several_tiles(G, B):
+    """Weight gradients of batches with more tiles than blocks (one to three a block) against the eight
+    parts of the batch, which take one each: the same mask in every part, so the mean over
+    eight times the cells scales each part's output gradient by exactly 1/8 and only the order of the
+    single-precision sums differs (up to 10^6 products of random sign: 1e-4 of a layer's norm)."""
+    dda = _dda()
+    g = torch.Generator("cuda").manual_seed(G)
+    n = B // 8
+    feat = torch.randn((8, n, G ** 3, 16), device="cuda", generator=g) * 0.5
+    feat[..., 0] = (torch.rand((n, G ** 3), device="cuda", generator=g) < 0.4).float()
+    feat = feat.to(torch.bfloat16)
+    tgt = torch.randn((8, n, G ** 3, 6), device="cuda", generator=g) * 0.3
+    with dda.Net(G, _params(8), max_batch=B) as net:
+        loss, grad = net.grad(feat.reshape(B, G ** 3, 16), tgt.reshape(B, G ** 3, 6))
+        parts = [net.grad(feat[i].contiguous(), tgt[i].contiguous()) for i in range(8)]
+    ref = np.mean([q.astype(np.float64) for _, q in parts], axis=0)
+    assert abs(loss - np.mean([v for v, _ in parts])) < 1e-6 * loss
+    off = 0
+    for li, (ci, co, *_) in enumerate(cn.LAYERS):
+        for k in (27 * ci * co, co):
+            a, b = grad[off:off + k].astype(np.float64), ref[off:off + k]
+            assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b) + 1e-12, (li, k)
+            off += k
