@@ -900,7 +900,8 @@ static dda_status refresh(Net &n) {
 }
 
 // one convolution launch; (cin, cout, up) picks the instantiation.  k_conv_rows where the weights fit
-// its registers, the box its tiles and the staged planes a quarter of a compute unit's LDS per block
+// its registers, the box its tiles and the staged planes 64 KiB of LDS, two blocks per compute unit or
+// more (32 channels: boxes up to 48, 16: up to 104)
 template <int CI, int CO, bool UPM> static bool conv_launch(const ConvArgs &p, hipStream_t s) {
     if constexpr (conv_rows_fits(CI)) {
         const size_t lds = conv_rows_lds(p.g, CI);

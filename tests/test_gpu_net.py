@@ -227,3 +227,32 @@ def test_blocks_that_take_several_tiles(G, B):
             a, b = grad[off:off + k].astype(np.float64), ref[off:off + k]
             assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b) + 1e-12, (li, k)
             off += k
+
+
+@pytest.mark.parametrize("G,grad", [(48, False), (56, False), (64, True)])
+def test_largest_boxes_of_the_tiled_kernels(G, grad):
+    """Three planes of 32 channels fit 64 KiB up to a side of 48 (56 takes the gathering kernel there), and
+    the weight gradient's two staged pairs per thread reach 64.  Bars as above."""
+    dda = _dda()
+    p = _params(9)
+    rng = np.random.default_rng(G)
+    f = rng.standard_normal((1, G, G, G, 16)) * 0.5
+    f[..., 0] = rng.random((1, G, G, G)) < 0.4
+    f = cn.bf16(f)
+    t = (rng.standard_normal((1, G, G, G, 6)) * 0.3).astype(np.float32)
+    feat = torch.from_numpy(f.astype(np.float32)).cuda().to(torch.bfloat16).reshape(1, G ** 3, 16)
+    with dda.Net(G, p, max_batch=1) as net:
+        if not grad:
+            o = net.forward(feat)[0].cpu().numpy().astype(np.float64).reshape(G, G, G, 6)
+            ref = cn.forward(p, f[0], bf16_round=True)["out"]
+            assert np.linalg.norm(o - ref) < 1e-2 * np.linalg.norm(ref)
+            return
+        loss, g = net.grad(feat, torch.from_numpy(t).cuda().reshape(1, G ** 3, 6))
+    lo, go = cn.loss_and_grad(p, f, t.astype(np.float64), f[..., 0], bf16_round=True)
+    assert abs(loss - lo) < 1e-2 * lo
+    off = 0
+    for li, (ci, co, *_) in enumerate(cn.LAYERS):
+        for n in (27 * ci * co, co):
+            a, b = g[off:off + n].astype(np.float64), go[off:off + n]
+            assert np.linalg.norm(a - b) <= 3e-2 * np.linalg.norm(b) + 1e-12, (li, n)
+            off += n
