@@ -35,13 +35,12 @@ template <typename R> constexpr int max_threads() { return sizeof(R) == 8 ? DDA_
 #define DDA_ZMUL_THREADS (3 * 64)  // block-size bound of the fused z-pass kernel
 #endif
 #ifndef DDA_TW_DERIVED
-#define DDA_TW_DERIVED 1  // radix-8 twiddles w^3, w^5, w^6, w^7 formed from w, w^2, w^4 (0: all from the table)
-#endif
-#ifndef DDA_B2_COLMAJOR
-#define DDA_B2_COLMAJOR 1  // y-pass output [Lx][c][Ly][nz] (0: [Ly][Lx][c][nz])
+// radix-8 twiddles w^3, w^5, w^6, w^7 formed from w, w^2, w^4 (0: all from the table) in the x and y passes,
+// the tensor's transform and the z pass planned at run time; the specialized z pass always forms them
+#define DDA_TW_DERIVED 1
 #endif
 #ifndef DDA_ZMUL_OWN
-#define DDA_ZMUL_OWN 1  // the fp64 z pass multiplies each thread's own component from registers
+#define DDA_ZMUL_OWN 1  // the fp64 z pass planned at run time multiplies each thread's own component from registers
 #endif
 #ifndef DDA_ZMUL_WAVES_PER_EU
 #define DDA_ZMUL_WAVES_PER_EU 3  // register budget of the z pass: three 3-wave blocks per CU at fp64

@@ -11,7 +11,7 @@
 //   compact vectors x, y     [c][N]                       (component-major)
 //   gmap                     [nz][ny][nx] int32: dipole index or -1 (void)
 //   B1 (after x pass)        [c][nz][Lx][ny]              y fastest
-//   B2 (after y pass)        [Ly][Lx][c][nz]              z fastest: a (kx, ky) column is contiguous
+//   B2 (after y pass)        [Lx][c][Ly][nz]              z fastest: a (kx, ky) column is contiguous
 //   Ghat octant              [Ly/2+1][Lx/2+1][6][Lz/2+1]  components xx, xy, xz, yy, yz, zz; a column's
 //                            six kz-runs are contiguous so a wave's tensor loads are unit-stride
 #pragma once
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_x(const int *__restric
 
 // ---------------------------------------------------------------- K2: forward y pass
 // Block: component c, column kx, NL consecutive planes z.  Reads B1 lines along y (n_y
-// nonzero entries), transforms, writes B2[ky][kx][c][z].
+// nonzero entries), transforms, writes B2[kx][c][ky][z].
 template <typename R, int LC, bool EXT>
 __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const int2 *__restrict__ ext, size_t rstride,
                                                 const cplx<R> *__restrict__ B1, cplx<R> *__restrict__ B2, int ny,
@@ -194,13 +194,7 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const int2 *__restri
     lds_passes<-1, kMaxRadix, LC, false>(lds + (t / TPL) * S, pl_rt, 1, NP - 1, t % TPL, tw);
     if constexpr (W) __syncthreads();  // the store mapping below crosses waves
     const int nzp = row_pitch(nz);
-#if DDA_B2_COLMAJOR
-    const size_t kystride = (size_t)nzp;
     C *dst = B2 + ((size_t)kx * ncomp + c) * (size_t)L * nzp;
-#else
-    const size_t kystride = (size_t)Lx * ncomp * nzp;
-    C *dst = B2 + ((size_t)kx * ncomp + c) * nzp;
-#endif
     if (NP >= 2) {
         const int line = t & (NL - 1), j = t >> lnl, z = z0 + line;
         const int Rp = RL, Ns = NSL;
@@ -208,12 +202,12 @@ __global__ void __launch_bounds__(max_threads<R>()) k_fwd_y(const int2 *__restri
             C a[kMaxRadix];
             const C *ln = lds + line * S;
             load_rt<-1, kMaxRadix>(a, Rp, jb, L, Ns, tw, [&](int i) { return ln[pidx(i)]; });
-            if (z < nz) store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) { st_stream(&dst[(size_t)i * kystride + z], v); });
+            if (z < nz) store_rt<kMaxRadix>(a, Rp, jb, Ns, [&](int i, C v) { st_stream(&dst[(size_t)i * nzp + z], v); });
         }
     } else {
         for (int e = t; e < NL * L; e += blockDim.x) {
             const int line = e & (NL - 1), i = e >> lnl, z = z0 + line;
-            if (z < nz) dst[(size_t)i * kystride + z] = lds[line * S + pidx(i)];
+            if (z < nz) dst[(size_t)i * nzp + z] = lds[line * S + pidx(i)];
         }
     }
 }
@@ -305,11 +299,7 @@ __global__ void __launch_bounds__(DDA_ZMUL_THREADS, DDA_ZMUL_WAVES_PER_EU) k_zmu
             const bool mxs = slot & 1, mys = slot & 2;
             const bool ok = (!mxs || nmx == 2) && (!mys || nmy == 2);  // slot holds a distinct column
             const int kx = mxs ? Lx - kxo : kxo, ky = mys ? Ly - kyo : kyo;
-#if DDA_B2_COLMAJOR
             C *line = B2 + (((size_t)(ok ? kx : 0) * (3 * nrhs) + rhs * 3 + comp) * Ly + (ok ? ky : 0)) * nzp;
-#else
-            C *line = B2 + (((size_t)(ok ? ky : 0) * Lx + (ok ? kx : 0)) * (3 * nrhs) + rhs * 3 + comp) * nzp;
-#endif
             for (int jb = j; jb < q0; jb += TPL) {
                 C a[kMaxRadixZ];
                 load_rt<-1, kMaxRadixZ, true>(a, R0, jb, L, 1, twp,
@@ -441,20 +431,14 @@ __global__ void __launch_bounds__(max_threads<R>()) k_inv_y(const int2 *__restri
     const int line = t / TPL, j = t % TPL, z = z0 + line;
     const int e = z < nz ? plane_range<EXT>(ext, (size_t)(c / 3) * rstride, z, ny) : 0;
     const int nzp = row_pitch(nz);
-#if DDA_B2_COLMAJOR
-    const size_t kystride = (size_t)nzp;
     const C *src = B2 + ((size_t)kx * ncomp + c) * (size_t)L * nzp;
-#else
-    const size_t kystride = (size_t)Lx * ncomp * nzp;
-    const C *src = B2 + ((size_t)kx * ncomp + c) * nzp;
-#endif
     {   // pass 0 from global, lanes over lines (z contiguous in B2)
         const int line = t & (NL - 1), j = t >> lnl, z = z0 + line;
         const bool zok = z < nz;
         for (int jb = j; jb < L / R0; jb += TPL) {
             C a[kMaxRadix];
             load_rt<+1, kMaxRadix>(a, R0, jb, L, 1, tw,
-                                   [&](int i) -> C { return zok ? ld_stream(&src[(size_t)i * kystride + z]) : czero<C>(); });
+                                   [&](int i) -> C { return zok ? ld_stream(&src[(size_t)i * nzp + z]) : czero<C>(); });
             C *ln = lds + line * S;
             store_rt<kMaxRadix>(a, R0, jb, 1, [&](int i, C v) { ln[pidx(i)] = v; });
         }

@@ -9,8 +9,9 @@
 // over-launching past convergence never changes its iterate.
 //
 // Vectors are [nrhs][3N] complex (component-major per RHS).  Reductions are per-block partial
-// sums in double precision, summed in a fixed order by one block per right-hand side, so results
-// are bitwise reproducible run to run.
+// sums in double precision, summed in a fixed order by every block of the kernel that needs them (or by
+// one block per right-hand side: initial and final sums, CGNR, the product's dots where they are many),
+// so results are bitwise reproducible run to run.
 #include <chrono>
 #include <cmath>
 #include <cstdio>
