@@ -51,10 +51,11 @@ constexpr int zcol_maxe(const FftPlan &p, int T) {
     return m;
 }
 
-// Products with their roundings spelled out: every lane, precision and batch size gets the same
-// values however the compiler arranges the kernel around them (the roundings are k_zmul's, so that
-// a solve's iterates do not depend on which of the two kernels ran).  The imaginary part rounds
-// a.x b.y (cmul1) or a.y b.x (cmul2) first.
+// Complex products with their fused multiply-adds spelled out, so that their roundings do not change with
+// how the compiler arranges the kernel around them (the additions of the butterflies are left to it; one
+// instantiation serves every batch, so a vector's product does not depend on the others).  The imaginary
+// part rounds a.x b.y (cmul1) or a.y b.x (cmul2) first; either would do, but an iterate of a slowly
+// converging solve depends on the choice, which therefore stays.
 template <typename R> __device__ __forceinline__ R fmar(R a, R b, R c) {
     if constexpr (sizeof(R) == 8) return __builtin_fma(a, b, c);
     else return __builtin_fmaf(a, b, c);
@@ -71,22 +72,6 @@ template <typename C> __device__ __forceinline__ C csqr(C a) {
 }
 // whether twiddle r of a radix-R pass is a product of table entries
 constexpr bool tw_derived(bool tw8, int R, int r) { return R == 8 && (tw8 ? r > 1 : r == 3 || r > 4); }
-
-// outputs 0..3 of dft8<+1> with the rotated terms rounded before they are added
-template <typename C> __device__ __forceinline__ void dft8_lower(C *a) {
-#pragma clang fp contract(off)
-    using R = decltype(C::x);
-    const R h = (R)0.70710678118654752440;
-    C e[4] = {a[0], a[2], a[4], a[6]};
-    C o[4] = {a[1], a[3], a[5], a[7]};
-    dft4<+1>(e);
-    dft4<+1>(o);
-    const C o1 = o[1], o3 = o[3];
-    a[0] = cadd(e[0], o[0]);
-    a[1] = mk<C>(e[1].x + (o1.x - o1.y) * h, e[1].y + (o1.x + o1.y) * h);
-    a[2] = cadd(e[2], mul_i<+1>(o[2]));
-    a[3] = mk<C>(e[3].x - (o3.x + o3.y) * h, e[3].y + (o3.x - o3.y) * h);
-}
 
 // w[r] = exp(-DIR 2 pi i r k step / L), r = 1..R-1
 template <int DIR, int R, bool TW8, typename C>
@@ -320,9 +305,7 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
 #pragma unroll
                         for (int r = 1; r < Rp; ++r) a[r] = cmul1(a[r], w[b][r]);
                     }
-                    // the rounding of k_zmul's last pass, which the compiler contracted at 64 and 160
-                    if constexpr (p + 1 == NP && NP > 1 && Rp == 8 && LC != 64 && LC != 160) dft8_lower(a);
-                    else dftR<+1, Rp>(a);
+                    dftR<+1, Rp>(a);
                 }
                 if constexpr (p + 1 < NP) {
                     lds_sync<true>();
