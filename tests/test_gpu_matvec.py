@@ -402,3 +402,53 @@ def test_axes_longer_than_256_cells_by_default(axis):
         x = inputs.random_vector(ctx.n, seed=6)
         y = ctx.matvec(inputs.X_POL, torch.from_numpy(x).cuda()).cpu().numpy()
     assert _rel_err(y, _oracle_y(mask, 1.4 + 0.02j, 0.5, inputs.X_POL, x)) < 1e-12
+
+
+@pytest.mark.parametrize("L", [32, 60, 72, 96, 160, 192, 256])
+def test_blocks_of_several_octant_columns(L):
+    """A plane of 128 x 128 padded columns has 4,225 octant columns: blocks of the z pass then take two to
+    five of them at these lengths and batches of 1, 3, 5 and 9 vectors (32: 3 5 3 3, 60: 5 3 1 1, 72: 3 1 1 2,
+    96: 5 3 1 1, 160: 3 1 3 1, 192: 1 2 2 1, 256: 1 2 2 2), and three or two leave one column to the last
+    block.  A batch equals its single products bit for bit, and those the oracle's: 1e-12 as above."""
+    dda = _dda()
+    mask = _random_mask((5, 64, 64), 900 + L, 0.03)  # [nz][ny][nx]
+    beams = [inputs.X_POL, inputs.Y_POL] * 5
+    with dda.Context(mask, 1.4 + 0.02j, 0.5, pad=(128, 128, L)) as ctx:
+        x = torch.from_numpy(inputs.random_vector(ctx.n, seed=L, n_rhs=9)).cuda()
+        one = torch.stack([ctx.matvec(beams[r], x[r].contiguous()) for r in range(9)])
+        for n in (3, 5, 9):
+            assert torch.equal(ctx.matvec_batch(beams[:n], x[:n].contiguous()), one[:n]), n
+        for r in (0, 1):
+            ref = _oracle_y(mask, 1.4 + 0.02j, 0.5, beams[r], x[r].cpu().numpy())
+            assert _rel_err(one[r].cpu().numpy(), ref) < 1e-12
+
+
+@pytest.mark.parametrize("nr", [60, 61, 240, 241])
+def test_scales_of_many_vectors(nr):
+    """The vectors' scales (four words each) travel as kernel arguments, 240 words a launch, up to 960 words,
+    and as a copy beyond: one and two launches, four, and the copy.  Every vector has a scale of its own
+    (oblique beams); each equals its single product bit for bit."""
+    dda = _dda()
+    mask = _random_mask((4, 5, 6), 51)
+    beams = inputs.beams_for_orientations(-(-nr // 2), seed=nr)[:nr]
+    with dda.Context(mask, 1.4 + 0.02j, 0.6) as ctx:
+        x = torch.from_numpy(inputs.random_vector(ctx.n, seed=3, n_rhs=nr)).cuda()
+        y = ctx.matvec_batch(beams, x)
+        for r in range(nr):
+            assert torch.equal(ctx.matvec(beams[r], x[r].contiguous()), y[r]), r
+    ref = _oracle_y(mask, 1.4 + 0.02j, 0.6, beams[nr - 1], x[nr - 1].cpu().numpy())
+    assert _rel_err(y[nr - 1].cpu().numpy(), ref) < 1e-12
+
+
+@pytest.mark.parametrize("nr", [10, 11, 40, 41])
+def test_polarizabilities_of_many_vectors_and_materials(nr):
+    """The same for the table of two materials (24 words a vector)."""
+    dda = _dda()
+    mask = _random_mask((4, 5, 6), 52)
+    mask[2:] *= 2
+    beams = inputs.beams_for_orientations(-(-nr // 2), seed=nr)[:nr]
+    with dda.Context(mask, [1.4 + 0.02j, 1.2], 0.6) as ctx:
+        x = torch.from_numpy(inputs.random_vector(ctx.n, seed=4, n_rhs=nr)).cuda()
+        y = ctx.matvec_batch(beams, x)
+        for r in range(nr):
+            assert torch.equal(ctx.matvec(beams[r], x[r].contiguous()), y[r]), r
