@@ -35,16 +35,28 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 KERNELS = ["fwd_x", "fwd_y", "zmul", "inv_y", "inv_x"]
 
 
-def alg_bytes(n, N, L, c, nrhs=1):
-    """Algorithmic bytes of one launch of each matvec kernel on an n^3 grid padded to L^3 for a
-    batch of nrhs vectors (c bytes per complex); the tensor octant is read once per batch."""
-    h = L // 2 + 1
+def lines_moved(mask, L, c, nrhs=1):
+    """Lines (y, z) of an n^3 grid padded to L^3 that the x and y passes move: all n^2, or, from 256 MB of
+    x-transformed planes on, those between the first and the last row with a dipole of each plane z."""
+    n = mask.shape[0]
+    if 3 * nrhs * n * L * (-(-n // 16) * 16) * c < 256 << 20:
+        return n * n
+    rows = mask.any(axis=2)  # [z][y]
+    first, last = rows.argmax(axis=1), n - rows[:, ::-1].argmax(axis=1)
+    return int((last - first)[rows.any(axis=1)].sum())
+
+
+def alg_bytes(mask, L, c, nrhs=1):
+    """Algorithmic bytes of one launch of each matvec kernel for a particle on an n^3 grid padded to L^3 and
+    a batch of nrhs vectors (c bytes per complex); the tensor octant is read once per batch, and lines of
+    planes that hold no dipole are not counted where the kernels leave them out."""
+    n, N, h, lines = mask.shape[0], int(np.count_nonzero(mask)), L // 2 + 1, lines_moved(mask, L, c, nrhs)
     return {
-        "fwd_x": c * nrhs * (3 * N + 3 * L * n * n),          # read x (non-void), write x-transformed planes
-        "fwd_y": c * nrhs * (3 * L * n * n + 3 * L * L * n),  # read, write y-transformed
+        "fwd_x": c * nrhs * (3 * N + 3 * L * lines),          # read x (non-void), write x-transformed planes
+        "fwd_y": c * nrhs * (3 * L * lines + 3 * L * L * n),  # read, write y-transformed
         "zmul": c * (nrhs * 2 * 3 * L * L * n + 6 * h ** 3),  # read + write the (kx, ky) columns, tensor octant
-        "inv_y": c * nrhs * (3 * L * L * n + 3 * L * n * n),
-        "inv_x": c * nrhs * (3 * L * n * n + 3 * N + 3 * N),  # read planes and x, write y (non-void)
+        "inv_y": c * nrhs * (3 * L * L * n + 3 * L * lines),
+        "inv_x": c * nrhs * (3 * L * lines + 3 * N + 3 * N),  # read planes and x, write y (non-void)
     }
 
 
@@ -564,7 +576,7 @@ def product_only(dda, inputs, torch, reps, n=256):
         x = torch.from_numpy(inputs.random_vector(N, seed=1, n_rhs=len(beams))).cuda()
         y = torch.empty_like(x)
         kms, tot = ctx.matvec_timed(beams, x, y, reps=reps)
-    ab = alg_bytes(n, N, L, 16, len(beams))
+    ab = alg_bytes(mask, L, 16, len(beams))
     return {"workload": f"{name}, fp64, batch of {len(beams)}", "padded": L, "n_dipoles": N, "tiles": tiles,
             "reps": reps, "total_ms": tot,
             "kernels": {k: {"ms": kms[i], "frac": ab[k] / kms[i] / 1e6 / HBM_PEAK_GBS} for i, k in enumerate(KERNELS)},
@@ -661,7 +673,7 @@ def main():
     x = torch.from_numpy(inputs.random_vector(N, seed=1, n_rhs=nb)).cuda()
     y = torch.empty_like(x)
     kms, tot_ms = ctx.matvec_timed(beams, x, y, reps=10)
-    ab = alg_bytes(n, N, L, 16, nb)
+    ab = alg_bytes(w.mask, L, 16, nb)
     per_kernel = {k: {"ms": kms[i], "alg_GB": ab[k] / 1e9, "GBps": ab[k] / kms[i] / 1e6,
                       "frac": ab[k] / kms[i] / 1e6 / HBM_PEAK_GBS} for i, k in enumerate(KERNELS)}
     dom = max(KERNELS, key=lambda k: per_kernel[k]["ms"])
@@ -670,7 +682,7 @@ def main():
     x32 = torch.from_numpy(inputs.random_vector(N, seed=1, n_rhs=nb).astype(np.complex64)).cuda()
     y32 = torch.empty_like(x32)
     kms32, tot32 = ctx.matvec_timed(beams, x32, y32, reps=10, precision=dda.FP32_REFINE)
-    ab32 = alg_bytes(n, N, L, 8, nb)
+    ab32 = alg_bytes(w.mask, L, 8, nb)
     per_kernel32 = {k: {"ms": kms32[i], "GBps": ab32[k] / kms32[i] / 1e6,
                         "frac": ab32[k] / kms32[i] / 1e6 / HBM_PEAK_GBS} for i, k in enumerate(KERNELS)}
     del x32, y32
