@@ -57,7 +57,7 @@ template <class K> inline void allow_lds(K kernel, size_t bytes) {
 // ceil(4 nrhs opb / (W CPW)) rounds.  The smallest opb whose estimate is not beaten by 10 %: turns of
 // the grid over the resident blocks, times rounds (a tenth for staging the tensor), times a factor
 // for the waves that share a compute unit.  A wave of 3, 5 or 7 columns needs several octant
-// columns to fill its rounds (L = 160, one vector: opb 1, 3: 127, 78 us; L = 96: opb 1, 5: 36,
+// columns to fill its rounds (L = 160, one vector: opb 1, 3: 96, 75 us; L = 96: opb 1, 5: 28,
 // 22 us), and small grids run faster with one block per compute unit.
 struct ZShape {
     int W, opb;

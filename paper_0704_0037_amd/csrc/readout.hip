@@ -177,9 +177,10 @@ __global__ void __launch_bounds__(512) k_ff_sum(const double2 *__restrict__ part
 
 // Stage 1 of the grouped sum: Q[vec][group][c][v][u] = sum over the cells a of the column (u, v) along
 // the axis of x exp(-i k w_g p_a), w_g the groups' direction component.  A block takes 64 columns
-// (neighbours along u) and four groups; its four waves split the column and are added in LDS.  Bound
-// by reading the vector once per four groups (128^3 sphere, one group, two vectors: 106 MB and
-// the cell map in 30 us).
+// (neighbours along u) and four groups; its four waves split the column and are added in LDS.  A lane's chain
+// of dependent loads (the cell map, then the vector) bounds it, eight rounds of four cells at 128, not the
+// bytes or the arithmetic: two vectors of the 128^3 sphere (106 MB and the map), one group, 29 us; with 2 % of
+// the cells filled 27; 24 and 19 if the three other groups' arithmetic is left out.
 constexpr int kFfGroups = 4;
 __global__ void __launch_bounds__(256) k_ff_collapse(const double2 *__restrict__ xa, const double2 *__restrict__ xb,
                                                      const int *__restrict__ gmap, int N, int nu, int nv, int na,
@@ -346,13 +347,16 @@ static dda_status farfield_sums(Ctx &c, const double2 *xa, const double2 *xb, in
     dda_status st;
     const int nvec = xb ? 2 : 1, e3 = 3 * ndir;
     const int n[3] = {c.nx, c.ny, c.nz};
-    // Work of the two ways, in lanes x cells: waves of directions over all dipoles; or, in runs along
-    // an axis, runs (in whole blocks of them) over all dipoles and waves of directions over the
-    // plane.  The second is taken where it does at most half the work (both inner loops run at about
-    // the same rate): 361 directions of the plane y = 0 on the 128^3 sphere, two vectors, 1515 ->
-    // 110 us, the asymmetry parameter of the 64^3 ellipsoid (21 rings of 42) 288 ->
-    // 78 us;
-    // directions in general position are a run each.
+    // Work of the two ways, in lanes x dipoles: waves of directions over all dipoles; or, in runs along
+    // an axis, runs (in whole blocks of them) over all dipoles and waves of directions over the cells of
+    // the plane.  The second is taken where it does at most half the work: 361 directions of the plane
+    // y = 0 on the 128^3 sphere, two vectors, 1515 -> 110 us, the asymmetry parameter of the 64^3 ellipsoid
+    // (21 rings of 42) 288 -> 78 us; directions in general position are a run each.
+    // The first stage walks void cells too, but they cost little beside its chain of loads: of 512 calls
+    // (cubes of 32 to 256 cells and slabs, 0.02 to 100 % filled, 1 to 40 rings of 20 to 400 directions) none
+    // that the rule sends here was faster in one stage (128^3, 4.4 %, 10 rings of 20: 185 and 92 us; 256^3,
+    // 1 %, 40 directions: 160 and 158), while a rule that counts every cell would keep 59 of them in one
+    // stage, at up to 3.9 times the time.
     FfRuns best;
     double cost = 0.5 * 64.0 * ((ndir + 63) / 64) * c.N;
     for (int a = 2; a >= 0; --a) {

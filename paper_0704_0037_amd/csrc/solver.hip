@@ -119,10 +119,10 @@ template <typename R> __device__ __forceinline__ double2 sum_dots(const cplx<R> 
 // that needs them: every block sums the partials itself, in the same order, and block 0 of the
 // right-hand side stores the scalars.  What other blocks of the kernel still read goes to a second
 // state (st2) that the next scalar kernel takes over, and partials go to a second array.  A scalar
-// kernel of its own (one block) cost 5 to 8 us of an iteration: it starts when the last block of the
-// pass before it has ended, and the next pass waits for it.  Per iteration of QMR, Bi-CG and Bi-CGSTAB,
-// with scalar kernels and without: 77, 67, 113 us and 58, 54, 88 (2,176 dipoles), 244, 231, 440 and
-// 229, 217, 416 (195,360 dipoles); from 380,000 dipoles on (1,024 blocks) even.
+// kernel of its own (one block) starts when the last block of the pass before it has ended, and the
+// next pass waits for it.  Per iteration of QMR, Bi-CG and Bi-CGSTAB in replayed graphs, with scalar kernels
+// and without: 42.0, 35.7, 74.3 us and 39.2, 33.9, 69.2 (2,176 dipoles), 205.6, 194.5, 382 and 204.0, 191.4,
+// 378 (195,360); at 463,400 dipoles (1,024 blocks) the same within 1 %.
 // Partials of the product that every block sums (2,352 at 735,904 dipoles, where both ways are even);
 // k_sum_dots sums more of them (24,576 at 256^3).
 constexpr int kBlockDots = 4096;

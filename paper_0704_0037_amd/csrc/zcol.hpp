@@ -11,16 +11,15 @@
 //     LDS line per column serves all components (a wave's LDS accesses complete in order, so the
 //     next component is written while the last one's reads are still on their way).
 // The bound is neither memory nor one unit: at L = 512 (two vectors, fp64, 14.5 GB) the vector unit
-// is busy 56 % of the time (2019 instructions per wave and column, 1728 of them fp64 arithmetic), LDS
-// 50 %, and memory runs at 3.9 TB/s of the 5.1 TB/s a copy reaches; the registers hold two waves per
+// is busy 55 % of the time (2045 instructions per wave and column, 1732 of them fp64 arithmetic), LDS
+// 48 %, and memory runs at 3.9 TB/s of the 5.1 TB/s a copy reaches; the registers hold two waves per
 // SIMD (three where noted below).  Measured per pass against one component per wave with the block
 // exchanging components through LDS (the kernel k_zmul, which the lengths planned at run time
-// keep), two vectors in fp64, spheres of m = 1.3:
-//   L      64   72   96  120  128  160  192  200  256   320   384   512
-//   was    21   40   56  100   99  227  364  437  695  1322  2019  4505 us
-//   is     15   25   38   70   68  160  244  325  494  1052  1615  3740 us
-// In fp32 (one vector) 192: 114 -> 66, 320: 454 -> 321, 512: 1198 -> 904 us.  At 32 and 48 (one
-// vector) the launch dominates and both take 10-11 us.
+// keep), two vectors in fp64, spheres of L / 2 cells, m = 1.3:
+//   L      32   48   64   72   96  120  128  160  192  200  256   320   384   512
+//   was    16   16   21   39   54   94   92  206  336  396  649  1292  2040  4439 us
+//   is     10   13   15   24   36   64   63  141  209  276  457   998  1588  3718 us
+// In fp32 (one vector) 64: 12 -> 11, 192: 105 -> 61, 320: 432 -> 284, 512: 1154 -> 875 us.
 #pragma once
 
 #include "fft.hpp"
@@ -104,21 +103,21 @@ __device__ __forceinline__ void zcol_tw(C *w, int k, int step, const C *tw) {
     }
 }
 
-// waves per SIMD that the registers are budgeted for: a third wave pays in fp64 where the kernel
-// fits 168 registers with at most a few spilled (two vectors, 2 against 3 waves: 192 254 -> 244 us,
-// 384 1830 -> 1615 us; but 160 160 -> 200 us, 512 3.74 -> 4.57 ms)
+// waves per SIMD that the registers are budgeted for: a third wave in fp64 where the kernel fits 168
+// registers with at most a few spilled (two vectors, 2 against 3 waves: 192 215 -> 208 us, 320 and 384 even;
+// but 160 141 -> 183 us, 512 3.72 -> 4.51 ms)
 template <typename R> constexpr int zcol_waves_per_simd(int L) {
     return sizeof(R) == 4 ? 4 : L == 192 || L == 320 || L == 384 ? 3 : 2;
 }
 // lengths whose budget holds only if the tensor loads of one frequency are not hoisted over the
-// products of the one before (192: 244 -> 216 us per two-vector fp64 pass; fp32 256: 144 -> 135 us)
+// products of the one before (192: 229 -> 208 us per two-vector fp64 pass, 384 1612 -> 1597, 320 even; fp32
+// within 2 % either way)
 template <typename R> constexpr bool zcol_fence(int L) {
     return sizeof(R) == 4 ? L > 128 : zcol_waves_per_simd<R>(L) == 3;
 }
 
 // lengths that load the first columns before the tensor is staged: there a block has one round and the
-// pass is a chain of latencies (32: a product of 25.3 -> 23.8 us; 48 with two vectors 13.7 -> 13.7, 64
-// 15.2 -> 15.5 us with the time to launch)
+// pass is a chain of latencies (32: 10.5 -> 10.0 us; 48 and 64: no change)
 constexpr bool zcol_ahead(int L) { return L <= 32; }
 
 template <typename R, int LC>
@@ -184,7 +183,7 @@ __global__ void __launch_bounds__(256, zcol_waves_per_simd<R>(LC))
     Item m = item_at(wave * CPW + slot);
     if constexpr (zcol_ahead(LC)) load_column(m, j0);
     {   // the tensor columns and the twiddles of the block.  fp32 keeps eight loads of a thread in
-        // flight (L = 256: 136 -> 128 us, 512: 999 -> 895 us); fp64, with half the waves, is 0-2 %
+        // flight (L = 256: 118 -> 114 us, 512: 1010 -> 891 us); fp64, with half the waves, is 0-2 %
         // faster loading one by one
         const C *gcol = Gh + (size_t)oct0 * 6 * HZ1;
         const int ng = nocc * 6 * HZ1;
