@@ -407,9 +407,23 @@ __global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr,
     const int rowp = 16 * xp;          // one row of 16 channels
     bf16 *xs = reinterpret_cast<bf16 *>(smem_wg);  // [3][6][16][xp]
     bf16 *gs = xs + 18 * rowp;                     // [4][16][xp]
+    int tile = blockIdx.x, last = tile;
+    if constexpr (MANY) {
+        tile = (int)((int64_t)blockIdx.x * ntile / gridDim.x);
+        last = (int)((int64_t)(blockIdx.x + 1) * ntile / gridDim.x) - 1;
+    }
     const int ytiles = g / 4, ztiles = (g + zchunk - 1) / zchunk;
-    int y0 = 0;
-    const bf16 *inb = in, *grb = gr;
+    int y0, z0, z1;
+    const bf16 *inb, *grb;
+    auto place = [&]() {
+        y0 = (tile % ytiles) * 4;
+        const int q = tile / ytiles, b = q / ztiles;
+        z0 = (q % ztiles) * zchunk;
+        z1 = min(g, z0 + zchunk);
+        inb = in + (size_t)b * gi * gi * gi * CIN + ci0;
+        grb = gr + (size_t)b * g * g * g * COUT + co0;
+    };
+    place();
     for (int e = t; e < 22 * rowp / 8; e += 192) reinterpret_cast<uint4 *>(xs)[e] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     // two neighbouring voxels' eight channels -> eight words [channel][x, x + 1]
@@ -465,19 +479,10 @@ __global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr,
     for (int k = 0; k < 9; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     Frag ones;
     ones.u = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-    int tile = blockIdx.x, last = tile;
-    if constexpr (MANY) {
-        tile = (int)((int64_t)blockIdx.x * ntile / gridDim.x);
-        last = (int)((int64_t)(blockIdx.x + 1) * ntile / gridDim.x) - 1;
-    }
-    do {
+    while (true) {
         // opaque from tile to tile: the staging addresses are formed in each instead of being held (which
         // would take a third of the waves)
         if constexpr (MANY) __asm__ volatile("" : "+v"(t));
-        y0 = (tile % ytiles) * 4;
-        const int q = tile / ytiles, z0 = (q % ztiles) * zchunk, z1 = min(g, z0 + zchunk), b = q / ztiles;
-        inb = in + (size_t)b * gi * gi * gi * CIN + ci0;
-        grb = gr + (size_t)b * g * g * g * COUT + co0;
         fetch_in(z0 - 1);
         put_in(0);
         fetch_in(z0);
@@ -517,7 +522,9 @@ __global__ void __launch_bounds__(192) k_wgrad_rows(const bf16 *__restrict__ gr,
             }
             __syncthreads();
         }
-    } while (MANY && ++tile <= last);
+        if (!MANY || ++tile > last) break;
+        place();
+    }
     // D: rows (output channels) 4 kg + i, column (input channel) lane & 15
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
